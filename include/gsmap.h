@@ -116,10 +116,12 @@ typedef struct gs_camera {
 
 /* Rasterizer settings, passed by host pointer and copied at each call.
  *   tile        screen tile edge in pixels: 8, 16 or 32
- *   lds_batch   Gaussians staged in LDS per batch: 128, 256 or 512
+ *   lds_batch   Gaussians staged in LDS per batch: 128, 256 or 512 (at tiles
+ *               8 and 16 at most block_threads are)
  *   block_threads  threads per tile workgroup (0 = default); each thread
  *               owns a vertical strip of tile*tile/block_threads pixels:
- *               tile 8: 64; tile 16: 64, 128 or 256 (default 64);
+ *               tile 8: 64; tile 16: 64, 128 or 256 (default by the number of
+ *               tiles);
  *               tile 32: 128 or 256 (default 256)
  *   bg          background colour added with weight T_final
  *   alpha_min   entries with alpha below this are skipped (1/255)

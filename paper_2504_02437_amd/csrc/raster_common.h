@@ -215,29 +215,61 @@ __device__ __forceinline__ void tile_range(const RasterArgs& a, int t,
   e = min((long long)a.ranges[2 * t + 1], a.key_cap);
 }
 
-inline int default_threads(int tile) { return tile == 32 ? 256 : 64; }
+// Launch shape of the compositing kernels for the caller's settings; results
+// do not depend on it.
+//
+// Threads the caller leaves open, tile 16: four small footprints per tile
+// (256 threads, one pixel each) while the tiles alone leave SIMDs idle and
+// the longest list's chain of entries is the time, then two, then the one
+// 16x16 footprint (64 threads, four pixels per lane) that issues the fewest
+// instructions per pair.  Forward / backward us, 64 against 128 against 256
+// threads: 300 tiles (320x240) 63 / 105, 42 / 70, 27 / 51; 1,700 tiles
+// (800x544) 109 / 187, 75 / 142, 67 / 132; 2,400 tiles (960x640) 79 / 153,
+// 70 / 139, 76 / 154; 4,800 tiles (4 views 640x480) 157 / 285, 138 / 258,
+// 150 / 297; 12,000 tiles (10 views 640x480) 197 / 377, 208 / 407, 261 / 534.
+//
+// Batch, tiles 8 and 16: at most one staged entry per thread.  A batch of
+// 256 in a one-wave workgroup holds 16 KB of LDS (the backward 28 KB), five
+// to ten waves per CU, too few to keep VALU issue busy (10 views 640x480, 64
+// threads, batch 256 against 64: forward 292 -> 194 us, backward's
+// compositing 660 -> 342 us).  At tile 32 larger batches pay (two barriers
+// per batch over four waves).
+struct RasterShape {
+  int tile, batch, threads;
+};
+
+inline RasterShape raster_shape(const gs_workspace* ws, const gs_settings* s) {
+  RasterShape r{ws->geo.tile, s->lds_batch, s->block_threads};
+  const long long tiles =
+      (long long)ws->geo.n_views * ws->tiles_x * ws->tiles_y;
+  if (r.threads == 0)
+    r.threads = r.tile == 32 ? 256
+                : r.tile == 8 || tiles >= 8192 ? 64
+                : tiles >= 2048 ? 128 : 256;
+  if (r.tile < 32 && r.batch > r.threads) r.batch = r.threads;
+  return r;
+}
 
 // Calls launcher.template go<TILE, BATCH, NT>() for a supported shape.
 template <typename Launcher>
-void dispatch_shape(int tile, int batch, int nt, const Launcher& l) {
-  if (nt == 0) nt = default_threads(tile);
-#define GS_BATCHES(T, N)                                  \
-  do {                                                    \
-    if (batch == 128) l.template go<T, 128, N>();         \
-    else if (batch == 256) l.template go<T, 256, N>();    \
-    else l.template go<T, 512, N>();                      \
-  } while (0)
-  if (tile == 8) {
-    GS_BATCHES(8, 64);
-  } else if (tile == 16) {
-    if (nt == 64) GS_BATCHES(16, 64);
-    else if (nt == 128) GS_BATCHES(16, 128);
-    else GS_BATCHES(16, 256);
+void dispatch_shape(const RasterShape& r, const Launcher& l) {
+  const int nt = r.threads;
+  if (r.tile == 8) {
+    l.template go<8, 64, 64>();
+  } else if (r.tile == 16) {
+    if (nt == 64) l.template go<16, 64, 64>();
+    else if (nt == 128) l.template go<16, 128, 128>();
+    else if (r.batch == 128) l.template go<16, 128, 256>();
+    else l.template go<16, 256, 256>();
+  } else if (nt == 128) {
+    if (r.batch == 128) l.template go<32, 128, 128>();
+    else if (r.batch == 256) l.template go<32, 256, 128>();
+    else l.template go<32, 512, 128>();
   } else {
-    if (nt == 128) GS_BATCHES(32, 128);
-    else GS_BATCHES(32, 256);
+    if (r.batch == 128) l.template go<32, 128, 256>();
+    else if (r.batch == 256) l.template go<32, 256, 256>();
+    else l.template go<32, 512, 256>();
   }
-#undef GS_BATCHES
 }
 
 }  // namespace gs

@@ -515,12 +515,11 @@ hipError_t launch_render_bwd(gs_workspace* ws, const gs_settings* s,
   } else {
     // The regulariser's workgroups (a grid stride over the Gaussians, as
     // many as its own launch would have) follow the tiles'.
-    const int nt = s->block_threads ? s->block_threads
-                                    : default_threads(ws->geo.tile);
+    const RasterShape shape = raster_shape(ws, s);
+    const int nt = shape.threads;
     const int pb = planar ? min(256, (planar->cap + nt - 1) / nt) : 0;
     const bool bg = s->bg[0] != 0.f || s->bg[1] != 0.f || s->bg[2] != 0.f;
-    dispatch_shape(ws->geo.tile, s->lds_batch, s->block_threads,
-                   BwdLauncher{a, tiles + pb, bg, st});
+    dispatch_shape(shape, BwdLauncher{a, tiles + pb, bg, st});
   }
   if (l1 && !l1->defer_reduce) {
     const hipError_t e = hipGetLastError();

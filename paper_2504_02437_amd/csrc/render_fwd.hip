@@ -339,7 +339,7 @@ hipError_t launch_render_fwd(gs_workspace* ws, const gs_settings* s,
   a.rgb = rgb; a.T = T; a.nlast = nlast; a.dom = nullptr; a.counts = nullptr;
   const int blocks = ws->geo.n_views * ws->tiles_x * ws->tiles_y;
   if (blocks <= 0) return hipSuccess;
-  dispatch_shape(ws->geo.tile, s->lds_batch, s->block_threads,
+  dispatch_shape(raster_shape(ws, s),
                  FwdLauncher<kRender>{a, blocks, st});
   return hipGetLastError();
 }
@@ -352,7 +352,7 @@ hipError_t launch_render_dominant(gs_workspace* ws, const gs_settings* s,
   a.rgb = rgb; a.T = T; a.nlast = nlast; a.dom = dom; a.counts = nullptr;
   const int blocks = ws->geo.n_views * ws->tiles_x * ws->tiles_y;
   if (blocks <= 0) return hipSuccess;
-  dispatch_shape(ws->geo.tile, s->lds_batch, s->block_threads,
+  dispatch_shape(raster_shape(ws, s),
                  FwdLauncher<kDominant>{a, blocks, st});
   return hipGetLastError();
 }
@@ -365,7 +365,7 @@ hipError_t launch_count_pairs(gs_workspace* ws, const gs_settings* s,
   a.counts = counts;
   const int blocks = ws->geo.n_views * ws->tiles_x * ws->tiles_y;
   if (blocks <= 0) return hipSuccess;
-  dispatch_shape(ws->geo.tile, s->lds_batch, s->block_threads,
+  dispatch_shape(raster_shape(ws, s),
                  FwdLauncher<kCount>{a, blocks, st});
   return hipGetLastError();
 }
