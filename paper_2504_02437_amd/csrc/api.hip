@@ -157,6 +157,8 @@ static int make_layout(const gs_geometry* g, Layout& L, int& tx, int& ty) {
   L.grad2d = take(V * 5 * cap * 4);
   L.gop = take(cap * 4);
   L.gcol = take(V * 3 * cap * 4);
+  L.gview = take(V * cap * 8 * 8);
+  L.gsum = take(cap * 4 * 8);
   L.shape = take(cap * (6 * 8 + 4 + 4));
   L.camd = take(V * kCamDoubles * sizeof(double));
   L.counters = take(sizeof(Counters));
@@ -190,7 +192,7 @@ int render_bwd_l1_checked(gs_workspace* ws, const gs_params* params,
                          const float* T_final, const int32_t* n_last,
                          gs_params* grad, double* loss_dev, double* sqerr_dev,
                          void* stream, const PlanarJob* planar,
-                         bool defer_reduce) {
+                         bool window) {
   g_err[0] = 0;
   if (int rc = check_ws(ws)) return rc;
   if (int rc = validate_params(params, "params")) return rc;
@@ -209,16 +211,16 @@ int render_bwd_l1_checked(gs_workspace* ws, const gs_params* params,
   if (int rc = same_layout(params, grad, "grad")) return rc;
   if (int rc = disjoint(params, "params", grad, "grad")) return rc;
   L1Fused l1{out_rgb, target, lambda, loss_dev, sqerr_dev};
-  l1.defer_reduce = defer_reduce;
+  l1.defer_reduce = window;
   return finish(launch_render_bwd(ws, s, nullptr, T_final, n_last, grad->rgb,
                                   params->sh_degree > 0, &l1,
-                                  (hipStream_t)stream, planar),
+                                  (hipStream_t)stream, planar, window),
                 "render_bwd_l1");
 }
 
 int project_bwd_checked(gs_workspace* ws, const gs_params* params,
                         const gs_camera* cams, gs_params* grad, void* stream,
-                        const L1ReduceJob* l1, bool cam_table) {
+                        const L1ReduceJob* l1, bool window) {
   g_err[0] = 0;
   if (int rc = check_ws(ws)) return rc;
   if (int rc = validate_params(params, "params")) return rc;
@@ -231,9 +233,9 @@ int project_bwd_checked(gs_workspace* ws, const gs_params* params,
   if (int rc = same_layout(params, grad, "grad")) return rc;
   if (int rc = disjoint(params, "params", grad, "grad")) return rc;
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = launch_project_bwd(ws, params, cams, grad, st, l1, cam_table);
+  hipError_t e = launch_project_bwd(ws, params, cams, grad, st, l1, window);
   if (e != hipSuccess) return finish(e, "project_bwd");
-  return finish(launch_sh_bwd(ws, params, cams, grad, st),
+  return finish(launch_sh_bwd(ws, params, cams, grad, st, window),
                 "view-dependent colour backward");
 }
 
@@ -370,6 +372,8 @@ int gs_workspace_create(const gs_geometry* geo, void* device_buffer,
   ws->grad2d = (float*)(b + L.grad2d);
   ws->gop = (float*)(b + L.gop);
   ws->gcol = (float*)(b + L.gcol);
+  ws->gview = (double*)(b + L.gview);
+  ws->gsum = (double*)(b + L.gsum);
   ws->shape = (double*)(b + L.shape);
   ws->camd = (double*)(b + L.camd);
   ws->counters = (Counters*)(b + L.counters);
@@ -379,6 +383,8 @@ int gs_workspace_create(const gs_geometry* geo, void* device_buffer,
   if (e == hipSuccess) e = launch_fill_u32(ws->grad2d, 0, V * 5 * cap, st);
   if (e == hipSuccess) e = launch_fill_u32(ws->gop, 0, cap, st);
   if (e == hipSuccess) e = launch_fill_u32(ws->gcol, 0, V * 3 * cap, st);
+  if (e == hipSuccess) e = launch_fill_u32(ws->gview, 0, V * cap * 16, st);
+  if (e == hipSuccess) e = launch_fill_u32(ws->gsum, 0, cap * 8, st);
   if (e == hipSuccess) e = launch_fill_u32(ws->counters, 0, sizeof(Counters) / 4, st);
   if (e == hipSuccess) e = launch_fill_u32(ws->ranges, 0, V * tx * ty * 2, st);
   if (e == hipSuccess) e = launch_iota_u32(ws->tile_order, V * tx * ty, st);

@@ -20,8 +20,8 @@ struct __align__(16) Record {
 struct Layout {
   size_t records, tiles_touched, rbox, depth, diff, ranges, cursor, tile_order,
       tile_loss, chunk_counts,
-      keys_unsorted, vals_sorted, keys_sorted, grad2d, gop, gcol, shape,
-      camd, counters, total;
+      keys_unsorted, vals_sorted, keys_sorted, grad2d, gop, gcol, gview,
+      gsum, shape, camd, counters, total;
 };
 
 // Binning works on chunks of Gaussians of one view (one workgroup each) with
@@ -100,6 +100,13 @@ struct gs_workspace {
                          // by the launch before the projection
   float* gcol;           // [V][3][capacity] dL/d colour per view (used with
                          // view-dependent colour)
+  // FP64 gradient accumulators laid out per Gaussian, so that a workgroup's
+  // adds for one entry fall in two lines instead of nine (render_bwd.hip);
+  // zero between calls.
+  double* gview;         // [V][capacity][8] dL/d(px, py, A, B, C), then
+                         // dL/d colour (view-dependent colour only)
+  double* gsum;          // [capacity][4] dL/d colour, dL/d opacity summed
+                         // over the views
   double* shape;         // [6][capacity] 3D covariance (upper triangle) of
                          // the last projection, then float opacity
                          // [capacity] and float log2(opacity) [capacity]
@@ -126,7 +133,7 @@ struct L1ReduceJob;    // tails.h
 hipError_t launch_project_bwd(gs_workspace* ws, const gs_params* p,
                               const gs_camera* cams, gs_params* grad,
                               hipStream_t st, const L1ReduceJob* l1 = nullptr,
-                              bool cam_table = false);
+                              bool window = false);
 hipError_t launch_bin(gs_workspace* ws, const gs_params* p, hipStream_t st);
 hipError_t launch_sort(gs_workspace* ws, const gs_settings* s, hipStream_t st);
 hipError_t launch_render_fwd(gs_workspace* ws, const gs_settings* s,
@@ -160,18 +167,22 @@ struct L1Fused {
 };
 // planar: the planar regulariser's workgroups appended to the launch (the
 // window graph), or null.
+// window: the gradients stay in the per-Gaussian accumulators (gview, gsum)
+// for launch_project_bwd's window form; else they end in grad2d, gop and
+// grad_rgb (or gcol).
 hipError_t launch_render_bwd(gs_workspace* ws, const gs_settings* s,
                              const float* dL, const float* T,
                              const int32_t* nlast, float* grad_rgb,
                              int per_view_colour, const L1Fused* l1,
-                             hipStream_t st, const PlanarJob* planar = nullptr);
+                             hipStream_t st, const PlanarJob* planar = nullptr,
+                             bool window = false);
 hipError_t launch_l1_reduce(const gs_workspace* ws, double* loss,
                             double* sqerr, hipStream_t st);
 hipError_t launch_sh_colour(gs_workspace* ws, const gs_params* p,
                             const gs_camera* cams, hipStream_t st);
 hipError_t launch_sh_bwd(gs_workspace* ws, const gs_params* p,
                          const gs_camera* cams, gs_params* grad,
-                         hipStream_t st);
+                         hipStream_t st, bool window = false);
 hipError_t launch_iota_u32(uint32_t* ptr, size_t count, hipStream_t st);
 hipError_t launch_fill_u32(void* ptr, uint32_t value, size_t count,
                            hipStream_t st);
@@ -187,21 +198,23 @@ hipError_t launch_adam(gs_params* p, const gs_params* g, gs_params* m,
                        float eps, int step, const int32_t* step_dev,
                        hipStream_t st, int step_bias = 0);
 // gs_render_bwd_l1 with its argument checks, the planar regulariser's
-// workgroups appended (or null) and the tile-loss reduction optionally left
-// to the caller.
+// workgroups appended (or null) and, for the window graph, the tile-loss
+// reduction left to the caller and the gradients left in the per-Gaussian
+// accumulators.
 int render_bwd_l1_checked(gs_workspace* ws, const gs_params* params,
                          const gs_settings* s, const float* out_rgb,
                          const float* target, float lambda,
                          const float* T_final, const int32_t* n_last,
                          gs_params* grad, double* loss_dev, double* sqerr_dev,
                          void* stream, const PlanarJob* planar,
-                         bool defer_reduce);
+                         bool window);
 // gs_project_bwd with its argument checks and an optional tile-loss
-// reduction workgroup; cam_table: the camera constants come from ws->camd
-// (formed from cams earlier in the same launch sequence).
+// reduction workgroup; window: the camera constants come from ws->camd
+// (formed from cams earlier in the same launch sequence) and the gradients
+// from the per-Gaussian accumulators.
 int project_bwd_checked(gs_workspace* ws, const gs_params* params,
                         const gs_camera* cams, gs_params* grad, void* stream,
-                        const L1ReduceJob* l1, bool cam_table = false);
+                        const L1ReduceJob* l1, bool window = false);
 // gs_planar_reg's argument checks; on success *job holds its launch.
 int planar_checked(const gs_params* params, float lambda, float floor_,
                    gs_params* grad, double* loss_dev, PlanarJob* job);

@@ -18,6 +18,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 #include "admit.h"
 #include "gs_internal.h"
 #include "shape.h"
@@ -322,7 +324,14 @@ struct ProjBwdArgs {
   float* d_lsc;
   float* d_quat;
   float* d_opl;
-  const double* camd;   // [V][kCamDoubles] (k_project_bwd<true>)
+  // The window graph's form (k_project_bwd<true>): camera constants [V]
+  // [kCamDoubles] and the per-Gaussian gradient accumulators in place of
+  // grad2d and gop, zeroed after reading; gsum's colour part is added to
+  // d_rgb.
+  const double* camd;
+  double2* gview;  // [V][cap][4]: (px, py), (A, B), (C, colour)
+  double2* gsum;   // [cap][2]: colour, opacity
+  float* d_rgb;
   // Workgroups past main_blocks reduce the fused L1 term's tile losses.
   int main_blocks;
   L1ReduceJob l1;
@@ -333,10 +342,14 @@ struct ProjBwdArgs {
 // matrix form: for the conic Q = Sigma2D^-1 the symmetric gradient is
 // G2 = -Q dQ Q; for Sigma2D = T Sigma T^T, dSigma = T^T G2 T and
 // dT = 2 G2 T Sigma; Sigma = M M^T gives dM = 2 dSigma M (summed over views).
-// TABLE: the views' FP64 camera constants come from a table formed earlier
-// in the launch sequence (scalar registers, no per-lane conversions).
-template <bool TABLE>
-__global__ __launch_bounds__(256) void k_project_bwd(ProjBwdArgs a) {
+// WINDOW: the views' FP64 camera constants come from a table formed earlier
+// in the launch sequence (scalar registers, no per-lane conversions), the
+// gradients from the per-Gaussian accumulators, of which only the binned
+// slots are read (64 bytes each; 74 us for 10 views and 300k Gaussians with
+// every slot read, 58 us).  Four waves per SIMD (14 spilled registers).
+template <bool WINDOW>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WINDOW ? 4 : 1)))
+void k_project_bwd(ProjBwdArgs a) {
   __shared__ double part[4];
   if ((int)blockIdx.x >= a.main_blocks) {   // dispatched last: the tail
     l1_reduce_part(a.l1, part);
@@ -366,33 +379,52 @@ __global__ __launch_bounds__(256) void k_project_bwd(ProjBwdArgs a) {
   // would take vector loads, the loop's stores keeping the compiler from
   // proving them read-only).
   ConstCamera* cams = (ConstCamera*)a.cams;
-  // Each view's tile count and five gradients are loaded one view ahead,
-  // so their latency overlaps the previous view's chain.
+  // Each view's five gradients are loaded one view ahead and its tile count
+  // two, so their latency overlaps the previous views' chains.
   int nx_binned = 0;
-  float nx[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+  using Grad = std::conditional_t<WINDOW, double, float>;
+  Grad nx[5] = {0, 0, 0, 0, 0};
+  auto ahead = [&](int k) {
+    if (WINDOW) {
+      if (nx_binned == 0) return;
+      const double2* p = a.gview + ((size_t)k * cap + g) * 4;
+      const double2 q = p[0], r = p[1];
+      nx[0] = q.x; nx[1] = q.y; nx[2] = r.x; nx[3] = r.y;
+      nx[4] = p[2].x;
+    } else {
+      const float* p = a.grad2d + (size_t)k * 5 * cap + g;
+      for (int i = 0; i < 5; ++i) nx[i] = p[(size_t)i * cap];
+    }
+  };
+  int nx2 = 0;
   if (a.V > 0) {
     nx_binned = a.tiles[g];
-    for (int i = 0; i < 5; ++i) nx[i] = a.grad2d[(size_t)i * cap + g];
+    if (a.V > 1) nx2 = a.tiles[(size_t)cap + g];
+    ahead(0);
   }
   for (int k = 0; k < a.V; ++k) {
     const int binned = nx_binned;
-    const float f0 = nx[0], f1 = nx[1], f2 = nx[2], f3 = nx[3], f4 = nx[4];
-    if (k + 1 < a.V) {
-      nx_binned = a.tiles[(size_t)(k + 1) * cap + g];
-      const float* gn = a.grad2d + (size_t)(k + 1) * 5 * cap + g;
-      for (int i = 0; i < 5; ++i) nx[i] = gn[(size_t)i * cap];
-    }
-    float* gk = a.grad2d + (size_t)k * 5 * cap + g;
-    const CamD cam = TABLE ? cam_d_table((ConstDouble*)a.camd + kCamDoubles * k)
-                           : cam_d(load_camera(cams + k));
+    const Grad f0 = nx[0], f1 = nx[1], f2 = nx[2], f3 = nx[3], f4 = nx[4];
+    nx_binned = nx2;
+    if (k + 2 < a.V) nx2 = a.tiles[(size_t)(k + 2) * cap + g];
+    if (k + 1 < a.V) ahead(k + 1);
+    const CamD cam = WINDOW ? cam_d_table((ConstDouble*)a.camd + kCamDoubles * k)
+                            : cam_d(load_camera(cams + k));
     // One test: a slot with no tiles or an all-zero gradient has nothing to
     // add (and nothing to clear).  (Bitwise, not short-circuit: the loads
     // must not wait on one another.)
     if ((binned == 0) | ((f0 == 0.f) & (f1 == 0.f) & (f2 == 0.f) &
                          (f3 == 0.f) & (f4 == 0.f)))
       continue;
-    gk[0] = 0.f; gk[cap] = 0.f; gk[2 * (size_t)cap] = 0.f;
-    gk[3 * (size_t)cap] = 0.f; gk[4 * (size_t)cap] = 0.f;
+    if (WINDOW) {
+      double2* p = a.gview + ((size_t)k * cap + g) * 4;
+      p[0] = p[1] = make_double2(0.0, 0.0);
+      p[2].x = 0.0;
+    } else {
+      float* gk = a.grad2d + (size_t)k * 5 * cap + g;
+      gk[0] = 0.f; gk[cap] = 0.f; gk[2 * (size_t)cap] = 0.f;
+      gk[3 * (size_t)cap] = 0.f; gk[4 * (size_t)cap] = 0.f;
+    }
     const double dpx = f0, dpy = f1, dA = f2, dB = f3, dC = f4;
     View P;
     make_view_grad(cam, mx, my, mz, Sig, shape_ok, P);
@@ -494,8 +526,19 @@ __global__ __launch_bounds__(256) void k_project_bwd(ProjBwdArgs a) {
   if (any)
     for (int j = 0; j < 4; ++j)
       a.d_quat[j * cap + g] += (float)((dq[j] - S.qn[j] * dot) / S.qnorm);
-  const double gop = a.gop[g];
-  a.gop[g] = 0.f;
+  double gop;
+  if (WINDOW) {
+    double2* p = a.gsum + 2 * (size_t)g;
+    const double2 q = p[0], r = p[1];
+    p[0] = p[1] = make_double2(0.0, 0.0);
+    a.d_rgb[g] += (float)q.x;
+    a.d_rgb[cap + g] += (float)q.y;
+    a.d_rgb[2 * (size_t)cap + g] += (float)r.x;
+    gop = r.y;
+  } else {
+    gop = a.gop[g];
+    a.gop[g] = 0.f;
+  }
   const double o = 1.0 / (1.0 + exp(-(double)a.opl[g]));
   a.d_opl[g] += (float)(gop * o * (1.0 - o));
 }
@@ -543,7 +586,7 @@ hipError_t launch_project(gs_workspace* ws, const gs_params* p,
 hipError_t launch_project_bwd(gs_workspace* ws, const gs_params* p,
                               const gs_camera* cams, gs_params* grad,
                               hipStream_t st, const L1ReduceJob* l1,
-                              bool cam_table) {
+                              bool window) {
   ProjBwdArgs a;
   a.mean = p->mean; a.lsc = p->log_scale; a.quat = p->quat;
   a.opl = p->opacity_logit; a.n_dev = p->n_dev; a.cap = p->capacity;
@@ -555,9 +598,11 @@ hipError_t launch_project_bwd(gs_workspace* ws, const gs_params* p,
   a.main_blocks = blocks;
   a.l1 = l1 ? *l1 : L1ReduceJob{};
   a.camd = ws->camd;
+  a.gview = (double2*)ws->gview; a.gsum = (double2*)ws->gsum;
+  a.d_rgb = grad->rgb;
   const int nb = blocks + (l1 ? 1 : 0);
   if (nb > 0) {
-    if (cam_table)
+    if (window)
       hipLaunchKernelGGL(k_project_bwd<true>, dim3(nb), dim3(256), 0, st, a);
     else
       hipLaunchKernelGGL(k_project_bwd<false>, dim3(nb), dim3(256), 0, st, a);

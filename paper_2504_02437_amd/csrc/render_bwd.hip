@@ -20,8 +20,8 @@
 // reduced over each 16-lane row with DPP (a transposed reduction that packs
 // four quantities into one register), merged across rows and waves by LDS
 // adds, and turned into the mean, conic and opacity gradients once per
-// entry and workgroup, which adds them to global memory with one atomic per
-// (entry, quantity).
+// entry and workgroup, which adds them to global memory (kSpreadPixels says
+// where).
 
 #include "raster_common.h"
 #include "tails.h"
@@ -39,6 +39,11 @@ struct BwdArgs {
   float* grgb;     // [3][cap] (caller's gradient rows, accumulated), or
                    // [V][3][cap] per view (view-dependent colour)
   size_t grgb_vstride;   // 0, or 3 cap for per-view colour gradients
+  // Per-Gaussian accumulators (not null: used in place of the above):
+  // gview [V][cap][8], gsum [cap][4]; view-dependent colour goes to gview.
+  double* gview;
+  double* gsum;
+  int view_colour;
   // L1 photometric term fused in (target not null): dL/dC is formed per
   // pixel from the forward's image instead of read from dL.
   const float* rgb;
@@ -431,7 +436,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(BG ? 1 : 5))
     }
     __syncthreads();
     // Per entry: the mean, conic and opacity gradients from the nine sums
-    // (A, B, C the unscaled conic, o the opacity), then one atomic each.
+    // (A, B, C the unscaled conic, o the opacity), then one atomic each:
+    // straight into the planar gradients, or back into the entry's LDS slot
+    // for the per-Gaussian accumulators.
     for (int jj = tid; jj < cnt; jj += NT) {
       const float* ac = acc[jj];
       const float s0 = ac[0], xs0 = ac[1], x2s0 = ac[2], s1 = ac[3];
@@ -448,6 +455,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(BG ? 1 : 5))
       val[6] = ac[6];
       val[7] = ac[7];
       val[8] = ac[8];
+      if (a.gview) {
+        float* out = acc[jj];
+#pragma unroll
+        for (int q = 0; q < 5; ++q) out[q] = val[q];
+        out[5] = val[6]; out[6] = val[7]; out[7] = val[8]; out[8] = val[5];
+        continue;
+      }
       const uint32_t g = gid[jj];
 #pragma unroll
       for (int q = 0; q < 9; ++q) {
@@ -457,7 +471,58 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(BG ? 1 : 5))
         else atomicAdd(&gc[(size_t)(q - 6) * r.cap + g], val[q]);
       }
     }
+    if (a.gview) {
+      // Nine consecutive lanes per entry: its adds fall in one 64-byte and
+      // one 32-byte piece, two requests to the memory side instead of nine.
+      __syncthreads();
+      double* gv = a.gview + (size_t)k * 8 * r.cap;
+      const float* flat = &acc[0][0];
+      for (int i = tid; i < cnt * 9; i += NT) {
+        const float val = flat[i];
+        if (val == 0.f) continue;
+        const int jj = i / 9, q = i - 9 * jj;
+        const size_t g = gid[jj];
+        const bool view = q < 5 || (q < 8 && a.view_colour);
+        atomicAdd(view ? gv + 8 * g + q : a.gsum + 4 * g + (q - 5), (double)val);
+      }
+    }
   }
+}
+
+// The per-Gaussian accumulators added to the planar gradients and cleared:
+// grid (Gaussians / 256, views).
+__global__ __launch_bounds__(256) void k_spread(BwdArgs a) {
+  const int g = blockIdx.x * 256 + threadIdx.x, k = blockIdx.y;
+  const size_t cap = a.r.cap;
+  if (g >= a.r.cap) return;
+  double2* p = (double2*)a.gview + (k * cap + g) * 4;
+  const double2 zero = make_double2(0.0, 0.0);
+  const double2 v0 = p[0], v1 = p[1], v2 = p[2], v3 = p[3];
+  const double v[8] = {v0.x, v0.y, v1.x, v1.y, v2.x, v2.y, v3.x, v3.y};
+  bool any = false;
+  float* gk = a.grad2d + k * 5 * cap + g;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    if (v[q] == 0.0) continue;
+    any = true;
+    float* out = q < 5 ? gk + q * cap
+                       : a.grgb + k * a.grgb_vstride + (q - 5) * cap + g;
+    *out += (float)v[q];
+  }
+  if (any) p[0] = p[1] = p[2] = p[3] = zero;
+  if (k != 0) return;
+  double2* s = (double2*)a.gsum + 2 * (size_t)g;
+  const double2 s0 = s[0], s1 = s[1];
+  const double t[4] = {s0.x, s0.y, s1.x, s1.y};
+  any = false;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (t[q] == 0.0) continue;
+    any = true;
+    float* out = q < 3 ? a.grgb + q * cap + g : a.gop + g;
+    *out += (float)t[q];
+  }
+  if (any) s[0] = s[1] = zero;
 }
 
 // Sum of the tiles' fused L1 losses into *loss and of each view's squared
@@ -466,6 +531,23 @@ __global__ __launch_bounds__(1024) void k_l1_reduce(L1ReduceJob j) {
   __shared__ double part[16];
   l1_reduce_part(j, part);
 }
+
+// Where the gradients go.  Straight into the planar rows, each entry of a
+// tile costs nine adds on nine lines, and a pass with many (tile, entry)
+// pairs is bound by them (about 55 G adds/s reach the memory side): 5.0 M
+// keys (10 views 640x480, tile 16) take 0.82 ms, of which 0.37 ms remain
+// with the adds left out; tile 32 has a third of the keys, 0.351 against
+// 0.344 ms.  Through the per-Gaussian accumulators the same pass takes 0.41
+// ms.  The window graph's projection backward reads the accumulators; the
+// entry points publish planar rows, so there a pass over the accumulators
+// follows (9 us at 300k Gaussians and one view), which pays at tiles below
+// 32 (1200x680, tile 16: 0.28 -> 0.164 ms with the pass; tile 32: 0.123 ms
+// either way) and images of this many pixels over all views (at 320x240 the
+// adds cost 2 us).  The accumulators are FP64: a Gaussian next to the camera
+// sums thousands of tiles' parts that mostly cancel, and FP32 adds in
+// whatever order they arrive left its gradient 1.4e-6 to 4.6e-6 off from run
+// to run (now 4.0e-7 on the same input, every run).
+constexpr long long kSpreadPixels = 400000;
 
 struct BwdLauncher {
   const BwdArgs& a;
@@ -489,7 +571,8 @@ hipError_t launch_render_bwd(gs_workspace* ws, const gs_settings* s,
                              const float* dL, const float* T,
                              const int32_t* nlast, float* grad_rgb,
                              int per_view_colour, const L1Fused* l1,
-                             hipStream_t st, const PlanarJob* planar) {
+                             hipStream_t st, const PlanarJob* planar,
+                             bool window) {
   BwdArgs a;
   a.r = make_raster_args(ws, s);
   a.dL = dL; a.Tfin = T; a.nlast = nlast;
@@ -504,6 +587,13 @@ hipError_t launch_render_bwd(gs_workspace* ws, const gs_settings* s,
   a.grad2d = ws->grad2d; a.gop = ws->gop;
   a.grgb = per_view_colour ? ws->gcol : grad_rgb;
   a.grgb_vstride = per_view_colour ? (size_t)3 * ws->geo.capacity : 0;
+  const long long pixels =
+      (long long)ws->geo.n_views * ws->geo.width * ws->geo.height;
+  const bool spread =
+      !window && ws->geo.tile < 32 && pixels >= kSpreadPixels;
+  const bool acc = window || spread;
+  a.gview = acc ? ws->gview : nullptr; a.gsum = acc ? ws->gsum : nullptr;
+  a.view_colour = per_view_colour;
   const int tiles = ws->geo.n_views * ws->tiles_x * ws->tiles_y;
   a.tile_blocks = tiles;
   a.planar = planar ? *planar : PlanarJob{};
@@ -520,6 +610,12 @@ hipError_t launch_render_bwd(gs_workspace* ws, const gs_settings* s,
     const int pb = planar ? min(256, (planar->cap + nt - 1) / nt) : 0;
     const bool bg = s->bg[0] != 0.f || s->bg[1] != 0.f || s->bg[2] != 0.f;
     dispatch_shape(shape, BwdLauncher{a, tiles + pb, bg, st});
+    if (spread && ws->geo.capacity > 0) {
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(k_spread, dim3((ws->geo.capacity + 255) / 256,
+                                        ws->geo.n_views), dim3(256), 0, st, a);
+    }
   }
   if (l1 && !l1->defer_reduce) {
     const hipError_t e = hipGetLastError();

@@ -20,6 +20,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 #include "gs_internal.h"
 
 namespace gs {
@@ -126,6 +128,7 @@ struct ShArgs {
   const int32_t* tiles;
   Record* rec;      // forward: colours overwritten
   float* gcol;      // backward: [V][3][cap], zeroed after reading
+  double* gview;    // backward, window graph: [V][cap][8], the colour at 5
   float* d_mean;
   float* d_rgb;
   float* d_sh;
@@ -173,7 +176,8 @@ __global__ __launch_bounds__(256) void k_sh_colour(ShArgs a) {
   }
 }
 
-template <int D>
+// WINDOW: the colour gradients come from the per-Gaussian accumulators.
+template <int D, bool WINDOW>
 __global__ __launch_bounds__(256) void k_sh_bwd(ShArgs a) {
   constexpr int NR = (D + 1) * (D + 1) - 1;
   const int g = blockIdx.x * 256 + threadIdx.x;
@@ -195,12 +199,15 @@ __global__ __launch_bounds__(256) void k_sh_bwd(ShArgs a) {
   for (int k = 0; k < a.V; ++k) {
     const size_t slot = (size_t)k * cap + g;
     if (a.tiles[slot] == 0) continue;
-    float* gk = a.gcol + (size_t)k * 3 * cap + g;
-    float gc[3] = {gk[0], gk[cap], gk[2 * (size_t)cap]};
+    using Grad = std::conditional_t<WINDOW, double, float>;
+    const size_t st = WINDOW ? 1 : cap;   // between channels
+    Grad* gk = WINDOW ? (Grad*)a.gview + slot * 8 + 5
+                      : (Grad*)a.gcol + (size_t)k * 3 * cap + g;
+    float gc[3] = {(float)gk[0], (float)gk[st], (float)gk[2 * st]};
     if (gc[0] == 0.f && gc[1] == 0.f && gc[2] == 0.f) continue;
-    gk[0] = 0.f;
-    gk[cap] = 0.f;
-    gk[2 * (size_t)cap] = 0.f;
+    gk[0] = 0;
+    gk[st] = 0;
+    gk[2 * st] = 0;
     any = true;
     float x, y, z, ir;
     view_dir(a.cams[k], mx, my, mz, x, y, z, ir);
@@ -244,6 +251,7 @@ ShArgs make_args(gs_workspace* ws, const gs_params* p, const gs_camera* cams) {
   a.mean = p->mean; a.rgb = p->rgb; a.sh = p->sh; a.n_dev = p->n_dev;
   a.cap = p->capacity; a.cams = cams; a.V = ws->geo.n_views;
   a.tiles = ws->tiles_touched; a.rec = ws->records; a.gcol = ws->gcol;
+  a.gview = ws->gview;
   a.d_mean = a.d_rgb = a.d_sh = nullptr;
   return a;
 }
@@ -265,15 +273,18 @@ hipError_t launch_sh_colour(gs_workspace* ws, const gs_params* p,
 
 hipError_t launch_sh_bwd(gs_workspace* ws, const gs_params* p,
                          const gs_camera* cams, gs_params* grad,
-                         hipStream_t st) {
+                         hipStream_t st, bool window) {
   ShArgs a = make_args(ws, p, cams);
   a.d_mean = grad->mean; a.d_rgb = grad->rgb; a.d_sh = grad->sh;
   const dim3 grid((p->capacity + 255) / 256), block(256);
   if (p->capacity <= 0 || p->sh_degree <= 0) return hipSuccess;
-  switch (p->sh_degree) {
-    case 1: hipLaunchKernelGGL(k_sh_bwd<1>, grid, block, 0, st, a); break;
-    case 2: hipLaunchKernelGGL(k_sh_bwd<2>, grid, block, 0, st, a); break;
-    default: hipLaunchKernelGGL(k_sh_bwd<3>, grid, block, 0, st, a); break;
+  switch (p->sh_degree * 2 + window) {
+    case 2: hipLaunchKernelGGL((k_sh_bwd<1, false>), grid, block, 0, st, a); break;
+    case 3: hipLaunchKernelGGL((k_sh_bwd<1, true>), grid, block, 0, st, a); break;
+    case 4: hipLaunchKernelGGL((k_sh_bwd<2, false>), grid, block, 0, st, a); break;
+    case 5: hipLaunchKernelGGL((k_sh_bwd<2, true>), grid, block, 0, st, a); break;
+    case 6: hipLaunchKernelGGL((k_sh_bwd<3, false>), grid, block, 0, st, a); break;
+    default: hipLaunchKernelGGL((k_sh_bwd<3, true>), grid, block, 0, st, a); break;
   }
   return hipGetLastError();
 }
