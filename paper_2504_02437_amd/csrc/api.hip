@@ -149,7 +149,7 @@ static int make_layout(const gs_geometry* g, Layout& L, int& tx, int& ty) {
   L.cursor = take(tiles * 4);
   L.tile_order = take(tiles * 4);
   L.tile_loss = take(tiles * 16);
-  const int ch = bin_chunk(tx, ty);
+  const int ch = bin_chunk(tx, ty, g->n_views, g->capacity);
   L.chunk_counts = take(ch ? V * ((cap + ch - 1) / ch) * (size_t)tx * ty * 4 : 0);
   L.keys_unsorted = take(kc * 8);
   L.vals_sorted = take(kc * 4);

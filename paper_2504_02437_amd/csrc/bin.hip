@@ -1,7 +1,7 @@
 // Tile binning: per-tile key counts, ranges, and the scatter of the
 // (depth, index) keys into their tiles' segments, without global atomics.
 //
-// Each workgroup owns a chunk of Gaussians of one view (1024 or 2048) and
+// Each workgroup owns a chunk of Gaussians of one view (512 to 2048) and
 // counts the chunk's keys per tile in LDS, walking the keys with wave-level
 // load balancing (one lane per key); the counts go to a [view][chunk][tile]
 // matrix.  A column scan over the chunks turns every entry into the chunk's
@@ -158,13 +158,29 @@ struct ScatterArgs {
   int order_n;                   // tiles to order in the scatter (0: none)
 };
 
-// Per-wave key enumeration: lane l owns one Gaussian with cnt keys (the tiles
-// of its render box, row-major); f(tile_in_view, g, depth_bits) runs once per key,
-// 64 keys per step, each lane locating its key's owner by binary search over
-// the wave's inclusive prefix of counts.
+// Per-wave key enumeration: lane l brings one Gaussian with cnt keys (the
+// tiles of its render box, row-major); f(tile_in_view, g, depth_bits) runs
+// once per key, 64 keys per step.  The lanes that have keys are packed into
+// a table of owners, and every owner sets the bit of its first key in a mask
+// over the next kSpanKeys keys; the owner of a key is then the number of set
+// bits up to it (one population count, no search), and its record one table
+// read.  What bounds the scatter is this chain of LDS round trips (owner,
+// counter) per 64 keys: with a binary search for the owner, six dependent
+// reads and an integer division, it took 79.6 us for 10 views of 1200x680
+// (9.5 M keys, tile 32), now 59 us; one view at tile 16 (2.9 M keys) 89.6 ->
+// 38 us.  Two steps in flight per wave take longer (65 us): the chip already
+// holds enough waves.
+struct __align__(16) Owner {
+  uint32_t start;   // first key
+  uint32_t xy;      // tile column | row << 16
+  uint32_t w;       // tile columns
+  uint32_t g;
+};
+constexpr int kSpanKeys = 2048;
 struct WaveOwners {
-  int incl[64], x0[64], y0[64], w[64];
-  uint32_t g[64], d[64];
+  Owner o[64];
+  float2 rd[64];    // 1 / w, depth bits
+  uint32_t first[kSpanKeys / 32];
 };
 
 // The binned tile box of (view k, Gaussian g) among the n live ones: its
@@ -222,23 +238,45 @@ __device__ inline void wave_enumerate(WaveOwners& O, int lane, int cnt, int x0,
     const int v = __shfl_up(s, off, 64);
     if (lane >= off) s += v;
   }
-  O.incl[lane] = s; O.x0[lane] = x0; O.y0[lane] = y0; O.w[lane] = w;
-  O.g[lane] = g; O.d[lane] = dbits;
-  wave_sync();
-  const int total = __shfl(s, 63, 64);
-  for (int b = 0; b < total; b += 64) {
-    const int j = b + lane;
-    if (j < total) {
-      int lo = 0, hi = 63;
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (O.incl[mid] > j) hi = mid; else lo = mid + 1;
+  const int total = __builtin_amdgcn_readlane(s, 63);
+  if (total == 0) return;
+  const uint32_t start = (uint32_t)(s - cnt);
+  const uint64_t has = __builtin_amdgcn_ballot_w64(cnt > 0);
+  if (cnt > 0) {
+    const int i = __builtin_amdgcn_mbcnt_hi(
+        (uint32_t)(has >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0));
+    O.o[i] = Owner{start, (uint32_t)x0 | ((uint32_t)y0 << 16), (uint32_t)w, g};
+    O.rd[i] = make_float2(1.f / (float)w, __uint_as_float(dbits));
+  }
+  int base = -1;   // owners that start before this step, less one
+  for (int b0 = 0; b0 < total; b0 += kSpanKeys) {
+    O.first[lane] = 0u;
+    wave_sync();
+    const uint32_t rel = start - (uint32_t)b0;
+    if (cnt > 0 && rel < kSpanKeys) atomicOr(&O.first[rel >> 5], 1u << (rel & 31));
+    wave_sync();
+    const uint32_t word = O.first[lane];
+    wave_sync();   // read before the next span clears it
+    const int steps = (min(total - b0, kSpanKeys) + 63) >> 6;
+    for (int q = 0; q < steps; ++q) {
+      const uint32_t lo = __builtin_amdgcn_readlane((int)word, 2 * q);
+      const uint32_t hi = __builtin_amdgcn_readlane((int)word, 2 * q + 1);
+      const uint32_t own = ((lane < 32 ? lo : hi) >> (lane & 31)) & 1u;
+      const int i = base + (int)own +
+                    (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+      base += __builtin_popcount(lo) + __builtin_popcount(hi);
+      const int j = b0 + 64 * q + lane;
+      if (j < total) {
+        const Owner o = O.o[i];
+        const float2 rd = O.rd[i];
+        // local / w by the reciprocal: the quotient's distance from an
+        // integer is at least 1 / (2 w) of the half-offset value, far above
+        // its rounding for local < 2^20.
+        const int local = j - (int)o.start;
+        const int ry = (int)(((float)local + 0.5f) * rd.x);
+        const int tx = (int)(o.xy & 0xffffu) + local - ry * (int)o.w;
+        f((int)((o.xy >> 16) + ry) * Tx + tx, o.g, __float_as_uint(rd.y));
       }
-      const int local = j - (lo ? O.incl[lo - 1] : 0);
-      const int ww = O.w[lo];
-      const int ty = O.y0[lo] + local / ww;
-      const int tx = O.x0[lo] + local % ww;
-      f(ty * Tx + tx, O.g[lo], O.d[lo]);
     }
   }
   wave_sync();   // the table is rewritten by the wave's next call
@@ -313,7 +351,7 @@ __global__ __launch_bounds__(1024) void k_chunk_scan(ChunkScanArgs a) {
   uint32_t* C = a.chunk_counts + (size_t)k * nch * nb;
   // The first kReg counts of the segment stay in registers between the two
   // passes, so the offsets are stored without a load before each store.
-  constexpr int kReg = 32;
+  constexpr int kReg = 40;
   uint32_t v[kReg];
   uint32_t sum = 0;
 #pragma unroll
@@ -372,8 +410,8 @@ __global__ __launch_bounds__(256) void k_scatter_chunks(ScatterArgs a) {
   const int bx = lid % (1 + a.nch), k = lid / (1 + a.nch);
   if (bx == 0) {
     if (k == 0 && a.order_n > 0)
-      order_tiles<256>(a.ranges, a.order, a.order_n, bins,
-                       (uint32_t*)owners[0].incl, (uint32_t*)owners[0].x0);
+      order_tiles<256>(a.ranges, a.order, a.order_n, bins, owners[0].first,
+                       owners[1].first);
     return;
   }
   const int chunk = bx - 1;
@@ -443,16 +481,6 @@ __global__ __launch_bounds__(256) void k_scatter_global(ScatterArgs a) {
                  });
 }
 
-// LDS per chunk-scatter workgroup, static and padding: three workgroups per
-// CU (160 KB).  Each XCD then has about 96 chunks in flight, whose key runs
-// share each tile's segment: the partly written lines of that frontier stay
-// in the XCD's 4 MB L2 until they fill and leave as whole lines.  With the
-// eight workgroups per CU that the registers allow, the frontier of about
-// 256 chunks outgrows the L2 and partial lines are written back (the
-// scatter of the 10-view 1200x680 window: 0.178 -> 0.166 ms for projection
-// and binning; two workgroups per CU, 0.186 ms, hide too little latency).
-constexpr size_t kScatterLds = 48 * 1024;
-
 constexpr int kOrderBuckets = 1024;
 constexpr int kOrderMaxTiles = 1 << 18;   // larger grids keep index order
 
@@ -460,6 +488,26 @@ __global__ void k_iota(uint32_t* p, size_t n) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n;
        i += (size_t)gridDim.x * blockDim.x)
     p[i] = (uint32_t)i;
+}
+
+// f(tile, list length) for every tile, the tiles dealt to the workgroup's
+// threads in turn.  The loads of kAhead rounds are in flight together: the
+// one workgroup that orders the tiles runs beside the scatter and has to end
+// before it.  With one load and wait per round it took 73 us for 12,000 tiles
+// (10 views 640x480, tile 16), longer than the scatter (52 us).
+template <int NT, typename F>
+__device__ __forceinline__ void each_length(const uint32_t* ranges, int n,
+                                            F&& f) {
+  constexpr int kAhead = 16;
+  for (int t0 = threadIdx.x; t0 < n; t0 += NT * kAhead) {
+    uint2 r[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      r[u] = ((const uint2*)ranges)[min(t0 + u * NT, n - 1)];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      if (t0 + u * NT < n) f(t0 + u * NT, r[u].y - r[u].x);
+  }
 }
 
 template <int NT>
@@ -474,11 +522,10 @@ __device__ void order_tiles(const uint32_t* ranges, uint32_t* order, int n,
   // The buckets span [shortest, longest], so few tiles share a bucket (and
   // its LDS counter).
   uint32_t mn = 0xffffffffu, mx = 0;
-  for (int t = tid; t < n; t += NT) {
-    const uint32_t len = ranges[2 * t + 1] - ranges[2 * t];
+  each_length<NT>(ranges, n, [&](int, uint32_t len) {
     mn = min(mn, len);
     mx = max(mx, len);
-  }
+  });
   for (int off = 32; off > 0; off >>= 1) {
     mn = min(mn, (uint32_t)__shfl_down((int)mn, off, 64));
     mx = max(mx, (uint32_t)__shfl_down((int)mx, off, 64));
@@ -486,10 +533,9 @@ __device__ void order_tiles(const uint32_t* ranges, uint32_t* order, int n,
   if ((tid & 63) == 0) { atomicMin(&mm[0], mn); atomicMax(&mm[1], mx); }
   __syncthreads();
   const uint32_t base = mm[0], width = (mm[1] - mm[0]) / kOrderBuckets + 1;
-  for (int t = tid; t < n; t += NT) {
-    const uint32_t b = (ranges[2 * t + 1] - ranges[2 * t] - base) / width;
-    atomicAdd(&cnt[kOrderBuckets - 1 - b], 1u);
-  }
+  each_length<NT>(ranges, n, [&](int, uint32_t len) {
+    atomicAdd(&cnt[kOrderBuckets - 1 - (len - base) / width], 1u);
+  });
   __syncthreads();
   // Exclusive scan of the bucket counts (longest bucket first): each thread
   // owns PER consecutive buckets.
@@ -515,10 +561,10 @@ __device__ void order_tiles(const uint32_t* ranges, uint32_t* order, int n,
     run += c[q];
   }
   __syncthreads();
-  for (int t = tid; t < n; t += NT) {
-    const uint32_t b = (ranges[2 * t + 1] - ranges[2 * t] - base) / width;
-    order[atomicAdd(&cnt[kOrderBuckets - 1 - b], 1u)] = (uint32_t)t;
-  }
+  each_length<NT>(ranges, n, [&](int t, uint32_t len) {
+    order[atomicAdd(&cnt[kOrderBuckets - 1 - (len - base) / width], 1u)] =
+        (uint32_t)t;
+  });
 }
 
 // Tiles by descending key count (a counting sort over 1024 length buckets)
@@ -560,11 +606,8 @@ hipError_t launch_chunked(const ScatterArgs& c, const RangeArgs& ra,
   cs.nch = nch;
   const int n = V * nb;
   cs.order_n = n <= kOrderMaxTiles ? n : 0;   // larger grids keep index order
-  // Padding LDS (unused) holds the scatter at three workgroups per CU.
-  constexpr size_t kStatic = MAXBINS * sizeof(uint32_t) + 4 * sizeof(WaveOwners);
-  const size_t pad = kStatic < kScatterLds ? kScatterLds - kStatic : 0;
   hipLaunchKernelGGL((k_scatter_chunks<MAXBINS, GPT>), dim3((1 + nch) * V),
-                     dim3(256), pad, st, cs);
+                     dim3(256), 0, st, cs);
   return hipGetLastError();
 }
 
@@ -591,7 +634,7 @@ hipError_t launch_bin(gs_workspace* ws, const gs_params* p, hipStream_t st) {
   c.keys = ws->keys_unsorted;
   c.key_cap = ws->geo.key_capacity;
   c.nch = 0; c.ranges = nullptr; c.order = nullptr; c.order_n = 0;
-  const int ch = bin_chunk(ws->tiles_x, ws->tiles_y);
+  const int ch = bin_chunk(ws->tiles_x, ws->tiles_y, V, p->capacity);
   const int cells = (ws->tiles_x + 1) * (ws->tiles_y + 1);
   if (ch && p->capacity <= 0) {
     // No Gaussians: every range is empty.
@@ -602,12 +645,16 @@ hipError_t launch_bin(gs_workspace* ws, const gs_params* p, hipStream_t st) {
   }
   // The chunked scatter also orders the tiles.
   c.ranges = ws->ranges; c.order = ws->tile_order;
-  if (ch == 1024)
+  if (ch && nb <= 1024 && cells <= 1024 + kGridSlack) {
+    if (ch == 512) return launch_chunked<1024, 2>(c, ra, ws->cursor, V, st);
     return launch_chunked<1024, 4>(c, ra, ws->cursor, V, st);
-  if (ch == 2048 && nb <= 4096 && cells <= 4096 + kGridSlack)
+  }
+  if (ch && nb <= 4096 && cells <= 4096 + kGridSlack) {
+    if (ch == 512) return launch_chunked<4096, 2>(c, ra, ws->cursor, V, st);
+    if (ch == 1024) return launch_chunked<4096, 4>(c, ra, ws->cursor, V, st);
     return launch_chunked<4096, 8>(c, ra, ws->cursor, V, st);
-  if (ch == 2048)
-    return launch_chunked<16384, 8>(c, ra, ws->cursor, V, st);
+  }
+  if (ch) return launch_chunked<16384, 8>(c, ra, ws->cursor, V, st);
   CountArgs ca;
   ca.diff = ws->diff; ca.counts = ws->cursor;
   ca.Tx = ws->tiles_x; ca.Ty = ws->tiles_y;
