@@ -2,10 +2,10 @@
 
 Every translation unit is compiled by hipcc for gfx950 only.  Packed FP32
 instructions are disabled for device code.  The projection, view-dependent
-colour and compositing units are compiled without FMA contraction: the
-projection so its FP64 front end rounds exactly in source order, the others
-so their forward and backward kernels take bit-identical decisions (they
-place FMAs explicitly).
+colour, nearest-mean and compositing units are compiled without FMA
+contraction: the projection and the nearest-mean distances so their FP64
+rounds exactly in source order, the others so their forward and backward
+kernels take bit-identical decisions (they place FMAs explicitly).
 """
 from __future__ import annotations
 
@@ -45,6 +45,7 @@ UNITS = [
     ("ssim.hip", []),
     ("densify.hip", []),
     ("mlp.hip", NO_CONTRACT),
+    ("near.hip", NO_CONTRACT),
     ("window.hip", []),
     ("noalloc.hip", []),
 ]

@@ -62,6 +62,9 @@ hipError_t launch_loss_colour(const float* rgb, const float* target, int V,
                               int fuse_l1, float* dL, double* loss,
                               double* sqerr, double* ssim, float* scratch,
                               hipStream_t st);
+hipError_t launch_nearest(const gs_params* p, const gs_camera* cam, int W,
+                          int H, const float* pts, int n_pts, int centre_only,
+                          unsigned long long* d2bits, hipStream_t st);
 hipError_t launch_knn_features(const gs_params* p, const gs_camera* cam, int W,
                                int H, const float* kf_rgb, const float* pts,
                                int n_pts, int centre_only, float* feats,
