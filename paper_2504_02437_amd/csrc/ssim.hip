@@ -7,348 +7,492 @@
 // B2 = var_x + var_y + C2 (C1 = 0.01^2, C2 = 0.03^2).  The loss adds
 // lam * sum over views of (1 - mean SSIM over 3HW).
 //
-// Two passes, both LDS-tiled and separable (a horizontal then a vertical
-// 11-tap pass over a tile plus its 5-pixel halo):
-//   k_ssim_stats: the five window sums, SSIM, its sum per view, and the
-//     three per-pixel derivatives dS/dmu_x, dS/dm_xx, dS/dm_xy (pre-scaled
-//     by -lam / 3HW) into the caller's scratch;
-//   k_ssim_grad: window sums of those three maps (the window is symmetric,
-//     so the adjoint of a window sum is a window sum), combined as
-//     dL/dx(p) += D1(p) + 2 x(p) D2(p) + y(p) D3(p).
+// The gradient is a second window sum: with D1, D2, D3 the per-pixel
+// derivatives of the term with respect to mu_x, the sum of x^2 (which equals
+// that of y^2) and the sum of x y, zero outside the image, and the window
+// symmetric, dL/dx(p) += D1(p) + 2 x(p) D2(p) + y(p) D3(p) over the windowed
+// maps.
+//
+// One pass (k_ssim): a workgroup walks down a strip of columns, four rows per
+// step.  Both window sums run vertically first, then horizontally.
+//   Vertical, one thread per column: four output rows of a map are a 4 x 14
+// band of weights times 14 input rows; the 4x4x1 matrix instruction (16
+// blocks of 4 rows x 4 columns, so that a lane's own column is its operand
+// and its result) adds one input row to four output rows, 14 instructions
+// where vector FMAs take 44, beside the vector unit.
+//   Horizontal, one thread per four columns of a row, which the threads
+// exchange through LDS: 14 reads serve 44 taps.
+// The images are read once (10 rows and columns of overlap around a strip),
+// the gradient is written once; the statistics need only four maps (x, y,
+// x^2 + y^2, x y), since the variances enter as a sum.
+//
+// Bound by the horizontal sums: 308 FMAs per four pixels in a row plus the
+// pointwise terms, about 500 vector instructions, at two waves per SIMD (220
+// registers for the two sets of 28 open sums; at three the sums spill, 2
+// times slower).  Two sets of LDS buffers instead of three, with a barrier
+// more per step, was 3 % slower.  In place of a statistics and a gradient
+// kernel with the derivative maps in memory between them: ten 680 x 1200 views
+// 282 us (was 405; 9.8 MB per plane in and out), one 44 (92), ten 480 x 640
+// 107 (161), one 251 x 377 17.3 (21.2), one 50 x 85 11.9 (12.5).
 
+#include <float.h>
 #include <math.h>
+
+#include <algorithm>
+#include <type_traits>
 
 #include "gs_internal.h"
 
 namespace gs {
 namespace {
 
-constexpr int kR = 5;                     // window radius (11 taps)
-constexpr int kTW = 64, kTH = 16;         // output tile
-constexpr int kIW = kTW + 2 * kR, kIH = kTH + 2 * kR;
-// LDS row strides padded so that the lanes of a half-wave in the horizontal
-// pass spread over the banks (hitem below).
-constexpr int kSW = kIW + 7;    // 81
-constexpr int kHW = kTW + 1;    // 65
-constexpr int kNT = 256;
-constexpr int kRunX = 8;                  // horizontal outputs per item
-constexpr int kRunY = kTH * kTW / kNT;    // vertical outputs per thread (4)
+typedef float f4v __attribute__((ext_vector_type(4)));
+
+constexpr int kR = 5;                   // window radius
+constexpr int kTaps = 2 * kR + 1;
+constexpr int kRows = 4;                // rows per step
+constexpr int kSpan = kTaps + kRows - 1;   // inputs of four outputs (14)
+constexpr int kLag = 6;                 // steps from a row's load to its output
 constexpr float kC1 = 0.01f * 0.01f, kC2 = 0.03f * 0.03f;
-static_assert(kTW * (kTH / kRunY) == kNT, "vertical pass layout");
 
 struct SsimArgs {
-  float w[2 * kR + 1];  // normalised 1D window
+  float w[kR + 1];      // normalised 1D window, taps 0 .. 5 (symmetric)
   const float* x;       // rendered [V][3][H][W]
   const float* y;       // target
   float* dL;            // [V][3][H][W], accumulated
-  float* scratch;       // [3][V*3][H][W]
   double* loss;
   double* ssim;         // [V] mean SSIM, accumulated (may be null)
   int V, H, W;
+  int strip, rows;      // output columns and rows of a workgroup
   float lam;
-  // L1 term fused in (l1 != 0): the statistics pass adds lam_l1 mean |x - y|
-  // to the loss and the squared errors to sqerr; the gradient pass WRITES
-  // dL = lam_l1 sign(x - y) / (3HW) + the SSIM gradient instead of adding
-  // to dL.
+  // L1 term fused in (l1 != 0): lam_l1 mean |x - y| is added to the loss and
+  // the squared errors to sqerr, and dL is WRITTEN as lam_l1 sign(x - y) /
+  // (3HW) + the SSIM gradient instead of added to.
   int l1;
+  int aligned;         // rows of 16-byte aligned groups of four pixels
   float l1_scale;      // lam_l1 / (3HW)
   double l1_lam_inv;   // lam_l1 / (3HW) in FP64
   double* sqerr;       // [V], may be null
 };
 
-// Work item it of a horizontal pass -> (halo row r, first output column
-// c0).  The 32 lanes of a half-wave take 8 rows x 4 runs: with row strides
-// of 17 and 1 modulo 32 (kSW, kHW) their LDS reads and writes fall in 32
-// distinct banks.  Items with r >= kIH have no row.
-constexpr int kHItems = 64 * ((kIH + 7) / 8);
-static_assert(kTW / kRunX == 8 && kSW % 32 == 17 && kHW % 32 == 1,
-              "horizontal-pass lane layout");
-__device__ inline void hitem(int it, int& r, int& c0) {
-  const int g = it >> 6, l = it & 63;
-  r = ((l & 31) >> 2) + 8 * g;
-  c0 = ((l & 3) + 4 * (l >> 5)) * kRunX;
-}
+// Vertical window sums of N maps, four rows at a time.  Group g holds the
+// output rows 4 g .. 4 g + 3 and takes the input rows 4 g .. 4 g + 13 (input
+// row n is output row n - 5).  Step s first adds two of its four input rows
+// to group s - 3, which is then finished, and afterwards all four to the
+// groups s - 2, s - 1 and s, the last in the registers of the finished one.
+// S: the step modulo 3, so that the groups' registers are constants of the
+// unrolled loop.  band: lane 4 k + i holds tap k - i, the weight of input row
+// k of a group for its output row i; the instruction broadcasts block k.
+// It multiplies every input row by every weight, and 0 times infinity or NaN
+// would reach output rows whose window does not hold that input.  Rows that
+// are not finite are therefore added as zeros and the windows that hold them
+// are set to NaN (what their statistics come to in any case).
+template <int N>
+struct VerticalSums {
+  f4v acc[N][3];
+  unsigned bad;   // bit b: the input row 3 - b (of this step) is not finite
+  // check: not finite where one of v is not.
+  __device__ __forceinline__ void screen(float check, float (&v)[kRows][N]) {
+    bad = (bad << kRows) & 0xffffu;
+    if (!__any(!(fabsf(check) <= FLT_MAX))) return;
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) {
+      bool finite = true;
+#pragma unroll
+      for (int m = 0; m < N; ++m) finite = finite && fabsf(v[j][m]) <= FLT_MAX;
+      bad |= finite ? 0u : 1u << (kRows - 1 - j);
+#pragma unroll
+      for (int m = 0; m < N; ++m) v[j][m] = finite ? v[j][m] : 0.f;
+    }
+  }
+  // Output row i of the finished group takes the input rows i - 12 .. i - 2.
+  template <int S>
+  __device__ __forceinline__ void mark() {
+    if (!__any(bad)) return;
+#pragma unroll
+    for (int i = 0; i < kRows; ++i)
+      acc[0][S][i] = bad & (0x7ffu << (5 - i)) ? NAN : acc[0][S][i];
+  }
+  template <int G, int K>
+  __device__ __forceinline__ void row(float band, const float (&v)[N]) {
+#pragma unroll
+    for (int m = 0; m < N; ++m) {
+      const f4v c = K == 0 ? f4v{0.f, 0.f, 0.f, 0.f} : acc[m][G];
+      acc[m][G] = __builtin_amdgcn_mfma_f32_4x4x1f32(band, v[m], c, 4, K, 0);
+    }
+  }
+  // Group s - 3, in the registers acc[..][S].
+  template <int S>
+  __device__ __forceinline__ void finish(float band, const float (&v)[kRows][N]) {
+    row<S, 12>(band, v[0]);
+    row<S, 13>(band, v[1]);
+    mark<S>();
+  }
+  template <int S>
+  __device__ __forceinline__ void add(float band, const float (&v)[kRows][N]) {
+    constexpr int P = (S + 2) % 3, Q = (S + 1) % 3;   // groups s - 1, s - 2
+    row<Q, 8>(band, v[0]);
+    row<P, 4>(band, v[0]);
+    row<S, 0>(band, v[0]);
+    row<Q, 9>(band, v[1]);
+    row<P, 5>(band, v[1]);
+    row<S, 1>(band, v[1]);
+    row<Q, 10>(band, v[2]);
+    row<P, 6>(band, v[2]);
+    row<S, 2>(band, v[2]);
+    row<Q, 11>(band, v[3]);
+    row<P, 7>(band, v[3]);
+    row<S, 3>(band, v[3]);
+  }
+};
 
-__device__ inline float block_sum(float v, float* part) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+// Four exchanged rows.  Column c (of the workgroup, from -8 on) at word c + 8
+// with one spare word after every fourth: the four-column reads of eight
+// lanes then fall in distinct banks.
+template <int NT>
+struct Exchange {
+  static constexpr int kWords = (NT + 16) * 5 / 4;
+  float4 v[kRows][kWords];
+  __device__ __forceinline__ static int at(int c) { return c + 8 + ((c + 8) >> 2); }
+  // Horizontal window sums of the columns 4 cg - 2 .. 4 cg + 1 of a row.
+  template <int N>
+  __device__ __forceinline__ void sums(int row, int cg, const float* w,
+                                       float (&out)[kRows][N]) const {
+    // kChunk inputs are read ahead of those in use (the scheduler would read
+    // all fourteen first, 56 registers).
+    constexpr int kChunk = 3;
+    const float4* p = &v[row][5 * cg];
+    float4 next[kChunk];
+#pragma unroll
+    for (int q = 0; q < kChunk; ++q) next[q] = p[1 + q + ((1 + q) >> 2)];
+#pragma unroll
+    for (int j0 = 0; j0 < kSpan; j0 += kChunk) {
+      float4 h[kChunk];
+#pragma unroll
+      for (int q = 0; q < kChunk; ++q) h[q] = next[q];
+#pragma unroll
+      for (int q = 0; q < kChunk; ++q) {
+        const int j = j0 + kChunk + q;
+        if (j < kSpan) next[q] = p[1 + j + ((1 + j) >> 2)];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < kChunk; ++q) {
+        const int j = j0 + q;
+        if (j >= kSpan) continue;
+        const float in[4] = {h[q].x, h[q].y, h[q].z, h[q].w};
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+          if (j < o || j - o >= kTaps) continue;
+#pragma unroll
+          for (int m = 0; m < N; ++m)
+            out[o][m] = j == o ? w[0] * in[m]
+                               : fmaf(w[min(j - o, 2 * kR - j + o)], in[m], out[o][m]);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+};
+
+// Sums over the workgroup in FP64, in thread 0.
+template <int N>
+__device__ inline void block_sums(double (&v)[N], double (*part)[N]) {
+  for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] += __shfl_down(v[k], off, 64);
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int k = 0; k < N; ++k) part[threadIdx.x >> 6][k] = v[k];
   __syncthreads();
-  float s = 0.f;
   if (threadIdx.x == 0)
-    for (int i = 0; i < kNT / 64; ++i) s += part[i];
-  return s;
+    for (int i = 1; i < (int)blockDim.x / 64; ++i)
+#pragma unroll
+      for (int k = 0; k < N; ++k) v[k] += part[i][k];
 }
 
-// Both passes: one plane per grid row; each workgroup takes every
-// gridDim.x-th tile of its plane, with the next tile's inputs loaded while
-// the current one is computed.  In the statistics pass the loss and the
-// per-view SSIM then take one FP64 atomic per workgroup rather than per tile
-// (atomics on one address serialise).
-__global__ __launch_bounds__(kNT) void k_ssim_stats(SsimArgs a) {
-  __shared__ float sx[kIH][kSW], sy[kIH][kSW];
-  __shared__ float hs[5][kIH][kHW];
-  __shared__ float part[kNT / 64];
+template <int NT>
+struct StripShared {
+  Exchange<NT> stat, d, der;
+  double part[NT / 64][3];
+};
+
+// What a thread keeps over the steps: as the thread of column u, and as the
+// row thread of four pixels from column uo on of every step's row `row`.
+struct StripState {
+  VerticalSums<4> stat;
+  VerticalSums<3> der;
+  float x[kRows], y[kRows];   // column u: the next four rows
+  unsigned in, out;      // row thread: bit o for a pixel of the image, the strip
+  float ss, ls;
+  double ssum, l1sum, sqsum;
+};
+
+// The image rows v0 - 10 + 4 s .. of column u (0 outside the image).
+__device__ __forceinline__ void load_rows(const SsimArgs& a, const float* X,
+                                          const float* Y, int v0, int s, int u,
+                                          StripState& st) {
+  const unsigned uc = (unsigned)min(max(u, 0), a.W - 1);
+  const bool col_in = u >= 0 && u < a.W;
+#pragma unroll
+  for (int j = 0; j < kRows; ++j) {
+    const int v = v0 - 2 * kR + kRows * s + j;   // uniform
+    const size_t o = (size_t)min(max(v, 0), a.H - 1) * a.W;
+    const bool in = col_in && v >= 0 && v < a.H;
+    const float x = (X + o)[uc], y = (Y + o)[uc];
+    st.x[j] = in ? x : 0.f;
+    st.y[j] = in ? y : 0.f;
+  }
+}
+
+// Step s (S: modulo 3): four image rows in, four rows of statistics (s - 3),
+// of derivative sums (s - 6) and of the gradient out.  PHASE 0, steps 0-2:
+// no statistics yet; 1, steps 3-5: no gradient yet; 2: all.
+template <int NT, int S, int PHASE>
+__device__ __forceinline__ void strip_step(const SsimArgs& a, const float* X,
+                                           const float* Y, float* G, int u0,
+                                           int u1, int v0, int v1, int s,
+                                           float band, float scale,
+                                           StripShared<NT>& sh, StripState& st) {
   const int tid = threadIdx.x;
-  const int plane = blockIdx.y;                 // view * 3 + channel
-  const int H = a.H, W = a.W;
-  const size_t HW = (size_t)H * W;
+  const int row = tid / (NT / 4), cg = tid % (NT / 4);
+  const int c0 = 4 * cg - 2;            // first column of the row thread
+  const int uo = u0 - 2 * kR + c0;      // its image column
+  // Vertical sums of the statistics.
+  {
+    float v[kRows][4];
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) {
+      v[j][0] = st.x[j];
+      v[j][1] = st.y[j];
+      v[j][2] = fmaf(st.x[j], st.x[j], st.y[j] * st.y[j]);
+      v[j][3] = st.x[j] * st.y[j];
+    }
+    load_rows(a, X, Y, v0, s + 1, u0 - 2 * kR + tid, st);
+    st.stat.screen((v[0][2] + v[1][2]) + (v[2][2] + v[3][2]), v);
+    if constexpr (PHASE >= 1) {
+      st.stat.template finish<S>(band, v);
+#pragma unroll
+      for (int i = 0; i < kRows; ++i)
+        sh.stat.v[i][Exchange<NT>::at(tid)] =
+            make_float4(st.stat.acc[0][S][i], st.stat.acc[1][S][i],
+                        st.stat.acc[2][S][i], st.stat.acc[3][S][i]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    st.stat.template add<S>(band, v);
+  }
+  if constexpr (PHASE == 0) return;
+  __syncthreads();
+  // Horizontal sums, SSIM and its derivatives.
+  {
+    float m[kRows][4];
+    sh.stat.template sums<4>(row, cg, a.w, m);
+    const int vs = v0 - kR + kRows * (s - 3) + row;
+    const float row_scale = vs >= 0 && vs < a.H ? scale : 0.f;
+    float rs = 0.f;
+#pragma unroll
+    for (int o = 0; o < 4; ++o) {
+      const float mx = m[o][0], my = m[o][1], mxy = mx * my;
+      const float mm = fmaf(mx, mx, my * my);
+      const float A1 = fmaf(2.f, mxy, kC1);
+      const float A2 = fmaf(2.f, m[o][3] - mxy, kC2);
+      const float B1 = mm + kC1;
+      const float B2 = (m[o][2] - mm) + kC2;
+      // Reciprocals are enough here (the term is compared at 1e-5 / 1e-3).
+      const float iB1 = __builtin_amdgcn_rcpf(B1), iB2 = __builtin_amdgcn_rcpf(B2);
+      const float iB = iB1 * iB2, A1B = A1 * iB, ssim = A2 * A1B;
+      rs += (st.out >> o) & 1 ? ssim : 0.f;
+      // dS/dmu_x = 2 (my (A2 - A1) / (B1 B2) + mx S (1 / B2 - 1 / B1)).
+      const float q = (st.in >> o) & 1 ? row_scale : 0.f, q2 = q + q;
+      float4 d;
+      d.x = q2 * fmaf(my * iB, A2 - A1, mx * ssim * (iB2 - iB1));
+      d.y = -q * (ssim * iB2);
+      d.z = q2 * A1B;
+      d.w = 0.f;
+      sh.d.v[row][Exchange<NT>::at(c0 + o)] = d;
+    }
+    st.ss += vs >= v0 && vs < v1 ? rs : 0.f;
+  }
+  __syncthreads();
+  // Vertical sums of the derivatives (their step s - 3, the same modulo 3).
+  {
+    float v[kRows][3];
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) {
+      const float4 d = sh.d.v[j][Exchange<NT>::at(tid)];
+      v[j][0] = d.x;
+      v[j][1] = d.y;
+      v[j][2] = d.z;
+    }
+    float check = 0.f;
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) check += (v[j][0] + v[j][1]) + v[j][2];
+    st.der.screen(check, v);
+    if constexpr (PHASE == 2) {
+      st.der.template finish<S>(band, v);
+#pragma unroll
+      for (int i = 0; i < kRows; ++i)
+        sh.der.v[i][Exchange<NT>::at(tid)] =
+            make_float4(st.der.acc[0][S][i], st.der.acc[1][S][i],
+                        st.der.acc[2][S][i], 0.f);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    st.der.template add<S>(band, v);
+  }
+  if constexpr (PHASE < 2) return;
+  // The gradient's four pixels of this row thread.
+  const int vo = v0 + kRows * (s - kLag) + row;
+  const bool any = vo < v1 && uo + 3 >= u0 && uo < u1;
+  float x[4] = {0.f, 0.f, 0.f, 0.f}, y[4] = {0.f, 0.f, 0.f, 0.f};
+  float g[4] = {0.f, 0.f, 0.f, 0.f};
+  const size_t po = (size_t)(vo * (long long)a.W + uo);
+  if (any && a.aligned) {   // all four pixels are the strip's
+    const float4 fx = *(const float4*)(X + po), fy = *(const float4*)(Y + po);
+    x[0] = fx.x; x[1] = fx.y; x[2] = fx.z; x[3] = fx.w;
+    y[0] = fy.x; y[1] = fy.y; y[2] = fy.z; y[3] = fy.w;
+    if (!a.l1) {
+      const float4 fg = *(const float4*)(G + po);
+      g[0] = fg.x; g[1] = fg.y; g[2] = fg.z; g[3] = fg.w;
+    }
+  } else if (any) {
+#pragma unroll
+    for (int o = 0; o < 4; ++o)
+      if (uo + o >= u0 && uo + o < u1) {
+        x[o] = X[po + o];
+        y[o] = Y[po + o];
+        if (!a.l1) g[o] = G[po + o];
+      }
+  }
+  __syncthreads();
+  float m[kRows][3];
+  sh.der.template sums<3>(row, cg, a.w, m);
+  if (!any) return;
+#pragma unroll
+  for (int o = 0; o < 4; ++o) {
+    if (a.l1) {   // pixels outside the strip hold x = y: nothing to add
+      const float e = x[o] - y[o];
+      g[o] = e > 0.f ? a.l1_scale : (e < 0.f ? -a.l1_scale : 0.f);
+      st.ls += fabsf(e);
+      st.sqsum += (double)e * (double)e;
+    }
+    const float t = fmaf(y[o], m[o][2], fmaf(2.f * x[o], m[o][1], m[o][0]));
+    g[o] = g[o] + t;
+  }
+  if (a.aligned) {
+    *(float4*)(G + po) = make_float4(g[0], g[1], g[2], g[3]);
+  } else {
+#pragma unroll
+    for (int o = 0; o < 4; ++o)
+      if (uo + o >= u0 && uo + o < u1) G[po + o] = g[o];
+  }
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT)
+void k_ssim(SsimArgs a) {
+  __shared__ StripShared<NT> sh;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int plane = blockIdx.z;                 // view * 3 + channel
+  const size_t HW = (size_t)a.H * a.W;
   const float* X = a.x + (size_t)plane * HW;
   const float* Y = a.y + (size_t)plane * HW;
-  const int tiles_x = (W + kTW - 1) / kTW;
-  const int tiles = tiles_x * ((H + kTH - 1) / kTH);
-  float w[2 * kR + 1];
+  float* G = a.dL + (size_t)plane * HW;
+  const int u0 = blockIdx.x * a.strip, v0 = blockIdx.y * a.rows;
+  const int u1 = min(a.W, u0 + a.strip), v1 = min(a.H, v0 + a.rows);
+  float band = 0.f;
 #pragma unroll
-  for (int i = 0; i < 2 * kR + 1; ++i) w[i] = a.w[i];
+  for (int t = 0; t < kTaps; ++t)
+    if ((lane >> 2) - (lane & 3) == t) band = a.w[min(t, 2 * kR - t)];
   const float n_inv = 1.f / (3.f * (float)HW);
   const float scale = -a.lam * n_inv;
-  float ssum = 0.f, l1sum = 0.f;
-  double sqsum = 0.0;
-  // The halo region of a tile is loaded into registers one tile ahead: the
-  // loads of the next tile are in flight while this one is computed.
-  constexpr int kLoads = (kIH * kIW + kNT - 1) / kNT;
-  float lx[kLoads], ly[kLoads];
-  auto fetch = [&](int tile) {
-    const int ou = (tile % tiles_x) * kTW, ov = (tile / tiles_x) * kTH;
+  StripState st;
+  st.ssum = st.l1sum = st.sqsum = 0.0;
+  st.stat.bad = st.der.bad = 0u;
 #pragma unroll
-    for (int j = 0; j < kLoads; ++j) {
-      const int i = tid + j * kNT;
-      const int r = i / kIW, c = i - r * kIW;
-      const int u = ou - kR + c, v = ov - kR + r;
-      const bool in = i < kIH * kIW && u >= 0 && u < W && v >= 0 && v < H;
-      lx[j] = in ? X[(size_t)v * W + u] : 0.f;
-      ly[j] = in ? Y[(size_t)v * W + u] : 0.f;
-    }
+  for (int g = 0; g < 3; ++g) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) st.stat.acc[m][g] = f4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int m = 0; m < 3; ++m) st.der.acc[m][g] = f4v{0.f, 0.f, 0.f, 0.f};
+  }
+  st.in = st.out = 0u;
+#pragma unroll
+  for (int o = 0; o < 4; ++o) {
+    const int u = u0 - 2 * kR - 2 + 4 * (tid % (NT / 4)) + o;
+    st.in |= (u >= 0 && u < a.W ? 1u : 0u) << o;
+    st.out |= (u >= u0 && u < u1 ? 1u : 0u) << o;
+  }
+  load_rows(a, X, Y, v0, 0, u0 - 2 * kR + tid, st);
+  const int steps = (v1 - v0 + kRows - 1) / kRows + kLag;
+  st.ss = st.ls = 0.f;
+  auto step = [&](auto S, auto P, int s) {
+    strip_step<NT, decltype(S)::value, decltype(P)::value>(
+        a, X, Y, G, u0, u1, v0, v1, s, band, scale, sh, st);
   };
-  if ((int)blockIdx.x < tiles) fetch(blockIdx.x);
-  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-    const int ou = (tile % tiles_x) * kTW, ov = (tile / tiles_x) * kTH;
-    __syncthreads();   // the previous tile's LDS reads are done
-#pragma unroll
-    for (int j = 0; j < kLoads; ++j) {
-      const int i = tid + j * kNT;
-      if (i < kIH * kIW) {
-        const int r = i / kIW, c = i - r * kIW;
-        sx[r][c] = lx[j];
-        sy[r][c] = ly[j];
-      }
-    }
-    __syncthreads();
-    if (tile + (int)gridDim.x < tiles) fetch(tile + gridDim.x);
-    // Horizontal pass: five sums for every row of the halo region.
-    for (int it = tid; it < kHItems; it += kNT) {
-      int r, c0;
-      hitem(it, r, c0);
-      if (r >= kIH) continue;
-      float px[kRunX + 2 * kR], py[kRunX + 2 * kR];
-      float pxx[kRunX + 2 * kR], pyy[kRunX + 2 * kR], pxy[kRunX + 2 * kR];
-#pragma unroll
-      for (int i = 0; i < kRunX + 2 * kR; ++i) {
-        px[i] = sx[r][c0 + i];
-        py[i] = sy[r][c0 + i];
-        pxx[i] = px[i] * px[i];
-        pyy[i] = py[i] * py[i];
-        pxy[i] = px[i] * py[i];
-      }
-#pragma unroll
-      for (int o = 0; o < kRunX; ++o) {
-        float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f, s4 = 0.f;
-#pragma unroll
-        for (int b = 0; b < 2 * kR + 1; ++b) {
-          const float wb = w[b];
-          s0 = fmaf(wb, px[o + b], s0);
-          s1 = fmaf(wb, py[o + b], s1);
-          s2 = fmaf(wb, pxx[o + b], s2);
-          s3 = fmaf(wb, pyy[o + b], s3);
-          s4 = fmaf(wb, pxy[o + b], s4);
-        }
-        hs[0][r][c0 + o] = s0; hs[1][r][c0 + o] = s1; hs[2][r][c0 + o] = s2;
-        hs[3][r][c0 + o] = s3; hs[4][r][c0 + o] = s4;
-      }
-    }
-    __syncthreads();
-    // Vertical pass: each thread finishes kRunY pixels of one column.
-    const int c = tid % kTW, r0 = (tid / kTW) * kRunY;
-    float* D1 = a.scratch + (size_t)plane * HW;
-    float* D2 = D1 + (size_t)a.V * 3 * HW;
-    float* D3 = D2 + (size_t)a.V * 3 * HW;
-    float col[5][kRunY + 2 * kR];
-#pragma unroll
-    for (int q = 0; q < 5; ++q)
-#pragma unroll
-      for (int i = 0; i < kRunY + 2 * kR; ++i) col[q][i] = hs[q][r0 + i][c];
-    const int u = ou + c;
-#pragma unroll
-    for (int o = 0; o < kRunY; ++o) {
-      float m[5];
-#pragma unroll
-      for (int q = 0; q < 5; ++q) {
-        float s = 0.f;
-#pragma unroll
-        for (int b = 0; b < 2 * kR + 1; ++b) s = fmaf(w[b], col[q][o + b], s);
-        m[q] = s;
-      }
-      const int v = ov + r0 + o;
-      if (u >= W || v >= H) continue;
-      if (a.l1) {
-        const float d = sx[kR + r0 + o][kR + c] - sy[kR + r0 + o][kR + c];
-        l1sum += fabsf(d);
-        sqsum += (double)d * (double)d;
-      }
-      const float mx = m[0], my = m[1];
-      const float A1 = 2.f * mx * my + kC1;
-      const float A2 = 2.f * (m[4] - mx * my) + kC2;
-      const float B1 = mx * mx + my * my + kC1;
-      const float B2 = (m[2] - mx * mx) + (m[3] - my * my) + kC2;
-      // Reciprocals are enough here (the term is compared at 1e-5 / 1e-3).
-      const float iA1 = __builtin_amdgcn_rcpf(A1), iA2 = __builtin_amdgcn_rcpf(A2);
-      const float iB1 = __builtin_amdgcn_rcpf(B1), iB2 = __builtin_amdgcn_rcpf(B2);
-      const float S = (A1 * A2) * (iB1 * iB2);
-      ssum += S;
-      const float d_mu = 2.f * S * (my * (iA1 - iA2) + mx * (iB2 - iB1));
-      const size_t p = (size_t)v * W + u;
-      D1[p] = scale * d_mu;
-      D2[p] = scale * (-S * iB2);
-      D3[p] = scale * (2.f * S * iA2);
-    }
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  step(I0{}, I0{}, 0);
+  step(I1{}, I0{}, 1);
+  step(I2{}, I0{}, 2);
+  step(I0{}, I1{}, 3);
+  step(I1{}, I1{}, 4);
+  step(I2{}, I1{}, 5);
+  for (int s = kLag; s < steps; s += 3) {
+    step(I0{}, I2{}, s);
+    if (s + 1 < steps) step(I1{}, I2{}, s + 1);
+    if (s + 2 < steps) step(I2{}, I2{}, s + 2);
+    st.ssum += (double)st.ss;
+    st.l1sum += (double)st.ls;
+    st.ss = st.ls = 0.f;
   }
-  const float tot = block_sum(ssum, part);
-  float l1tot = 0.f;
-  double sqtot = 0.0;
-  if (a.l1) {
-    __syncthreads();
-    l1tot = block_sum(l1sum, part);
-    __shared__ double dpart[kNT / 64];
-    for (int off = 32; off > 0; off >>= 1) sqsum += __shfl_down(sqsum, off, 64);
-    if ((tid & 63) == 0) dpart[tid >> 6] = sqsum;
-    __syncthreads();
-    if (tid == 0)
-      for (int i = 0; i < kNT / 64; ++i) sqtot += dpart[i];
-  }
+  double sum[3] = {st.ssum, st.l1sum, st.sqsum};
+  block_sums(sum, sh.part);
   if (tid == 0) {
     const int k = plane / 3;
-    atomicAdd(a.loss, -(double)a.lam * (double)tot * (double)n_inv +
-                          (double)l1tot * a.l1_lam_inv);
-    if (a.l1 && a.sqerr) atomicAdd(&a.sqerr[k], sqtot);
-    if (a.ssim) atomicAdd(&a.ssim[k], (double)tot * (double)n_inv);
-    if (plane == 0 && blockIdx.x == 0)
+    atomicAdd(a.loss, -(double)a.lam * sum[0] * (double)n_inv + sum[1] * a.l1_lam_inv);
+    if (a.l1 && a.sqerr) atomicAdd(&a.sqerr[k], sum[2]);
+    if (a.ssim) atomicAdd(&a.ssim[k], sum[0] * (double)n_inv);
+    if (plane == 0 && blockIdx.x == 0 && blockIdx.y == 0)
       atomicAdd(a.loss, (double)a.lam * a.V);
   }
 }
 
-__global__ __launch_bounds__(kNT) void k_ssim_grad(SsimArgs a) {
-  __shared__ float sd[3][kIH][kSW];
-  __shared__ float hs[3][kIH][kHW];
-  const int tid = threadIdx.x;
-  const int plane = blockIdx.y;
-  const int H = a.H, W = a.W;
-  const size_t HW = (size_t)H * W;
-  const size_t PL = (size_t)a.V * 3 * HW;
-  const float* D = a.scratch + (size_t)plane * HW;
-  const int tiles_x = (W + kTW - 1) / kTW;
-  const int tiles = tiles_x * ((H + kTH - 1) / kTH);
-  float w[2 * kR + 1];
-#pragma unroll
-  for (int i = 0; i < 2 * kR + 1; ++i) w[i] = a.w[i];
-  // This thread's output pixels: column c, rows r0 .. r0 + kRunY - 1.
-  const int c = tid % kTW, r0 = (tid / kTW) * kRunY;
-  const float* X = a.x + (size_t)plane * HW;
-  const float* Y = a.y + (size_t)plane * HW;
-  float* G = a.dL + (size_t)plane * HW;
-  // A tile's inputs (the derivative maps over the halo region, and x, y and
-  // dL at this thread's pixels) are loaded into registers one tile ahead.
-  constexpr int kLoads = (kIH * kIW + kNT - 1) / kNT;
-  float ld[3][kLoads];
-  float xo[kRunY], yo[kRunY], go[kRunY];
-  auto fetch = [&](int tile) {
-    const int ou = (tile % tiles_x) * kTW, ov = (tile / tiles_x) * kTH;
-    const int u = ou + c;
-#pragma unroll
-    for (int o = 0; o < kRunY; ++o) {
-      const int v = ov + r0 + o;
-      const bool in = u < W && v < H;
-      const size_t p = (size_t)v * W + u;
-      xo[o] = in ? X[p] : 0.f;
-      yo[o] = in ? Y[p] : 0.f;
-      go[o] = (in && !a.l1) ? G[p] : 0.f;
-    }
-#pragma unroll
-    for (int j = 0; j < kLoads; ++j) {
-      const int i = tid + j * kNT;
-      const int r = i / kIW, cc = i - r * kIW;
-      const int uu = ou - kR + cc, vv = ov - kR + r;
-      const bool in = i < kIH * kIW && uu >= 0 && uu < W && vv >= 0 && vv < H;
-      const size_t p = (size_t)vv * W + uu;
-#pragma unroll
-      for (int q = 0; q < 3; ++q) ld[q][j] = in ? D[q * PL + p] : 0.f;
-    }
-  };
-  if ((int)blockIdx.x < tiles) fetch(blockIdx.x);
-  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-    const int ou = (tile % tiles_x) * kTW, ov = (tile / tiles_x) * kTH;
-    const int u = ou + c;
-    float x0[kRunY], y0[kRunY], g0[kRunY];
-#pragma unroll
-    for (int o = 0; o < kRunY; ++o) {
-      x0[o] = xo[o];
-      y0[o] = yo[o];
-      if (a.l1) {
-        const float d = xo[o] - yo[o];
-        g0[o] = d > 0.f ? a.l1_scale : (d < 0.f ? -a.l1_scale : 0.f);
-      } else {
-        g0[o] = go[o];
+// How the planes are split: threads of a workgroup (20 columns more than it
+// writes) and the rows that it writes.
+struct Split {
+  int nt, strips, rows;
+};
+
+// The split of the least cost, in steps of a workgroup.  A workgroup takes
+// five steps' time to its first output and one per four rows from there.  A
+// SIMD holds two waves (registers) and a step of two takes 1.3 times as long
+// as a step of one (a 680 x 1200 view by 256 threads: 252 workgroups of 52 rows
+// take 49 us, 396 of 32 rows 44 us).
+// Workgroups add their sums to the same addresses, 10 ns each (a 251 x 377
+// view: 567 workgroups of 64 threads with eight steps' time, 22.4 us; 432 with
+// nine, 22.4 us).
+Split split_planes(int planes, int H, int W) {
+  const int groups = (H + kRows - 1) / kRows;
+  Split best{};
+  double least = 0.0;
+  for (int nt = 64; nt <= 256; nt *= 2) {
+    const int strips = (W + nt - 4 * kR - 1) / (nt - 4 * kR);
+    const long long columns = (long long)strips * planes;
+    const long long filled = 1024 / (nt / 64);   // workgroups: a wave per SIMD
+    for (int r = 1; r <= 16; ++r) {
+      const long long parts = std::max(filled * r / columns, 1LL);
+      const int g = (int)((groups + parts - 1) / parts);
+      const long long n = columns * ((groups + g - 1) / g);
+      const long long waves = (n + filled - 1) / filled;
+      const double cost = (waves / 2 * 1.3 + waves % 2) * (g + kLag - 1) + 0.0075 * n;
+      if (!best.nt || cost < least) {
+        best = {nt, strips, kRows * g};
+        least = cost;
       }
-    }
-    __syncthreads();   // the previous tile's LDS reads are done
-#pragma unroll
-    for (int j = 0; j < kLoads; ++j) {
-      const int i = tid + j * kNT;
-      if (i < kIH * kIW) {
-        const int r = i / kIW, cc = i - r * kIW;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) sd[q][r][cc] = ld[q][j];
-      }
-    }
-    __syncthreads();
-    if (tile + (int)gridDim.x < tiles) fetch(tile + gridDim.x);
-    for (int it = tid; it < kHItems; it += kNT) {
-      int r, c0;
-      hitem(it, r, c0);
-      if (r >= kIH) continue;
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        float pv[kRunX + 2 * kR];
-#pragma unroll
-        for (int i = 0; i < kRunX + 2 * kR; ++i) pv[i] = sd[q][r][c0 + i];
-#pragma unroll
-        for (int o = 0; o < kRunX; ++o) {
-          float s = 0.f;
-#pragma unroll
-          for (int b = 0; b < 2 * kR + 1; ++b) s = fmaf(w[b], pv[o + b], s);
-          hs[q][r][c0 + o] = s;
-        }
-      }
-    }
-    __syncthreads();
-    float col[3][kRunY + 2 * kR];
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-#pragma unroll
-      for (int i = 0; i < kRunY + 2 * kR; ++i) col[q][i] = hs[q][r0 + i][c];
-#pragma unroll
-    for (int o = 0; o < kRunY; ++o) {
-      float m[3];
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        float s = 0.f;
-#pragma unroll
-        for (int b = 0; b < 2 * kR + 1; ++b) s = fmaf(w[b], col[q][o + b], s);
-        m[q] = s;
-      }
-      const int v = ov + r0 + o;
-      if (u >= W || v >= H) continue;
-      G[(size_t)v * W + u] = g0[o] + (m[0] + 2.f * x0[o] * m[1] + y0[o] * m[2]);
     }
   }
+  return best;
 }
 
 }  // namespace
@@ -379,23 +523,40 @@ hipError_t launch_loss_colour(const float* rgb, const float* target, int V,
       g[i] = exp(-d * d / (2.0 * 1.5 * 1.5));
       sum += g[i];
     }
-    for (int i = 0; i < 2 * kR + 1; ++i) a.w[i] = (float)(g[i] / sum);
+    for (int i = 0; i <= kR; ++i) a.w[i] = (float)(g[i] / sum);
   }
-  a.x = rgb; a.y = target; a.dL = dL; a.scratch = scratch; a.loss = loss;
+  a.x = rgb; a.y = target; a.dL = dL; a.loss = loss;
   a.ssim = ssim; a.V = V; a.H = H; a.W = W; a.lam = lam;
   const size_t per = (size_t)3 * H * W;
   a.l1 = fuse_l1;
   a.l1_scale = (float)((double)lam_l1 / (double)per);
   a.l1_lam_inv = (double)lam_l1 / (double)per;
   a.sqerr = sqerr;
-  const dim3 grid((W + kTW - 1) / kTW, (H + kTH - 1) / kTH, V * 3);
-  const int tiles = (int)(grid.x * grid.y);
-  hipLaunchKernelGGL(k_ssim_stats, dim3(min(tiles, 64), V * 3), dim3(kNT), 0,
-                     st, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_ssim_grad, dim3(min(tiles, 64), V * 3), dim3(kNT), 0,
-                     st, a);
+  // Workgroups read pixels whose gradients others write: a gradient written
+  // over one of the images goes by way of the scratch.
+  const size_t bytes = per * V * sizeof(float);
+  auto over = [&](const float* p) {
+    const uintptr_t i = (uintptr_t)p, g = (uintptr_t)dL;
+    return i < g + bytes && g < i + bytes;
+  };
+  if (dL != scratch && (over(rgb) || over(target))) {
+    if (hipError_t e = hipMemcpyAsync(scratch, dL, bytes, hipMemcpyDeviceToDevice, st)) return e;
+    if (hipError_t e = launch_loss_colour(rgb, target, V, H, W, lam_l1, lam, fuse_l1,
+                                          scratch, loss, sqerr, ssim, scratch, st))
+      return e;
+    return hipMemcpyAsync(dL, scratch, bytes, hipMemcpyDeviceToDevice, st);
+  }
+  a.aligned = (W & 3) == 0 &&
+              (((uintptr_t)rgb | (uintptr_t)target | (uintptr_t)dL) & 15) == 0;
+  const Split split = split_planes(3 * V, H, W);
+  a.strip = ((W + split.strips - 1) / split.strips + 3) & ~3;
+  a.rows = split.rows;
+  const dim3 grid(split.strips, (H + a.rows - 1) / a.rows, V * 3);
+  switch (split.nt) {
+    case 64: hipLaunchKernelGGL(k_ssim<64>, grid, dim3(64), 0, st, a); break;
+    case 128: hipLaunchKernelGGL(k_ssim<128>, grid, dim3(128), 0, st, a); break;
+    default: hipLaunchKernelGGL(k_ssim<256>, grid, dim3(256), 0, st, a); break;
+  }
   return hipGetLastError();
 }
 

@@ -1,0 +1,99 @@
+"""Structural-similarity kernel at the edges of its strips and row groups.
+
+A workgroup writes a strip of 44, 108 or 236 columns at most and a multiple of
+four rows of a plane; shapes on both sides of those lines, of several
+workgroups per column and of widths that are no multiple of four (scalar
+writes instead of groups of four) are compared with the FP64 oracle, at the
+bounds of the other shapes: the sums of 121 products of FP32 numbers below one
+are good to 121 * 2^-24 = 7e-6, and to 1e-5 where the terms of both signs of a
+view's mean average out; a gradient takes two of them, divided by C2 = 9e-4 or
+more, to 1e-3 of the larger gradients."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2504_02437_amd import raster as R
+from test_gpu_ssim import _check, _colour, _pair
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 3, 11, 44), (1, 3, 12, 45), (1, 3, 13, 88), (1, 3, 5, 108),
+          (1, 3, 16, 109), (2, 3, 31, 216), (1, 3, 33, 217), (1, 3, 9, 236),
+          (1, 3, 50, 237), (4, 3, 150, 473), (1, 3, 330, 44)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_strip_edges_against_the_oracle(shape):
+    x, y = _pair(11, shape)
+    print("case ssim strip", shape, flush=True)
+    _check(x, y)
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_strip_edges_fused_equals_l1_then_ssim(shape):
+    x, y = _pair(12, shape)
+    print("case colour strip", shape, flush=True)
+    a = _colour(x, y, 0.8, 0.2, False)
+    b = _colour(x, y, 0.8, 0.2, True)
+    assert b[0] == pytest.approx(a[0], rel=1e-6)
+    np.testing.assert_allclose(b[1], a[1], rtol=1e-12)
+    np.testing.assert_allclose(b[2], a[2], rtol=1e-12)
+    np.testing.assert_array_equal(b[3], a[3])
+
+
+@pytest.mark.parametrize("which", range(3))
+def test_misaligned_images(which):
+    """One of the three images four bytes off a 16-byte line: the same
+    gradient as aligned (the same sums, written one by one)."""
+    shape = (1, 3, 21, 240)
+    x, y = _pair(13, shape)
+    n = x.size
+    buf = [torch.zeros(n + 4, device="cuda") for _ in range(3)]
+    loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+    ref = _colour(x, y, 0.8, 0.2, True)
+    t = [b[int(i == which):][:n].view(shape) for i, b in enumerate(buf)]
+    t[0].copy_(torch.from_numpy(x))
+    t[1].copy_(torch.from_numpy(y))
+    print("case colour misaligned", which, flush=True)
+    R.loss_colour(t[0], t[1], 0.8, 0.2, t[2], loss)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(t[2].cpu().numpy(), ref[3])
+    assert all(float(b[-1]) == 0.0 for b in buf)
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("at", [(37, 120), (0, 0), (43, 1)])
+def test_a_value_that_is_not_finite_stays_in_its_windows(at, value):
+    """A gradient depends on the pixels at most ten rows and columns away:
+    NaN there, and bit for bit as without the value further off."""
+    x, y = _pair(14, (1, 3, 61, 250))
+    good = _colour(x, y, 0.8, 0.2, True)[3][0, 1]
+    x[0, 1, at[0], at[1]] = value
+    print("case colour not finite", at, value, flush=True)
+    loss, _, _, g = _colour(x, y, 0.8, 0.2, True)
+    r, c = np.mgrid[0:61, 0:250]
+    near = np.maximum(abs(r - at[0]), abs(c - at[1])) <= 10
+    assert np.isnan(loss)
+    assert np.isnan(g[0, 1][near]).all()
+    np.testing.assert_array_equal(g[0, 1][~near], good[~near])
+    assert np.isfinite(g[0, 0]).all() and np.isfinite(g[0, 2]).all()
+
+
+@pytest.mark.parametrize("shape", [(2, 3, 30, 300), (1, 3, 9, 45)])
+@pytest.mark.parametrize("fused", [False, True])
+def test_gradient_written_over_the_rendering(shape, fused):
+    """dL in the memory of the rendered images: as with memory of its own."""
+    x, y = _pair(15, shape)
+    xd, yd = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+    own = xd.clone()
+    loss = torch.zeros(2, dtype=torch.float64, device="cuda")
+    print("case colour in place", shape, fused, flush=True)
+    if fused:
+        R.loss_colour(xd, yd, 0.8, 0.2, own, loss[:1])
+        R.loss_colour(xd, yd, 0.8, 0.2, xd, loss[1:])
+    else:
+        R.loss_ssim(xd, yd, 0.2, own, loss[:1])
+        R.loss_ssim(xd, yd, 0.2, xd, loss[1:])
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(xd.cpu().numpy(), own.cpu().numpy())
+    assert float(loss[0]) == pytest.approx(float(loss[1]), rel=1e-9)
