@@ -41,33 +41,38 @@ __device__ inline float admit_level(const Record& R, int iu0, int iu1, int iv0,
 // Minimum of q(d) over the rectangle [dx0, dx1] x [dy0, dy1] (A, C > 0 and a
 // positive definite form): 0 if the rectangle holds the origin, else the
 // smallest of the four edge minima (each a clamped 1D quadratic).  FP64.
-__device__ inline double qmin_rect(double A, double B, double C, double dx0,
-                                   double dx1, double dy0, double dy1) {
+// sx = -B / A and sy = -B / C: where the form is smallest along a row and
+// along a column, per unit of the other offset.
+__device__ inline double qmin_rect(double A, double B, double C, double sx,
+                                   double sy, double dx0, double dx1,
+                                   double dy0, double dy1) {
   if (dx0 <= 0.0 && 0.0 <= dx1 && dy0 <= 0.0 && 0.0 <= dy1) return 0.0;
   double best = INFINITY;
   const double xs[2] = {dx0, dx1}, ys[2] = {dy0, dy1};
   for (int i = 0; i < 2; ++i) {
     const double dx = xs[i];
-    const double dy = fmin(fmax(-B * dx / C, dy0), dy1);
+    const double dy = fmin(fmax(sy * dx, dy0), dy1);
     best = fmin(best, (A * dx + 2.0 * B * dy) * dx + C * dy * dy);
   }
   for (int i = 0; i < 2; ++i) {
     const double dy = ys[i];
-    const double dx = fmin(fmax(-B * dy / A, dx0), dx1);
+    const double dx = fmin(fmax(sx * dy, dx0), dx1);
     best = fmin(best, (A * dx + 2.0 * B * dy) * dx + C * dy * dy);
   }
   return best;
 }
 
 // Whether the ellipse q(d) <= L can hold a pixel of the pixel rectangle
-// [u0, u1] x [v0, v1] of record R.
-__device__ inline bool ellipse_meets(const Record& R, float L, int u0, int u1,
-                                     int v0, int v1) {
+// [u0, u1] x [v0, v1] of record R.  sx, sy: qmin_rect's, formed once per
+// record by the caller, who asks for several rectangles.
+__device__ inline bool ellipse_meets(const Record& R, float L, double sx,
+                                     double sy, int u0, int u1, int v0,
+                                     int v1) {
   if (u0 > u1 || v0 > v1 || L < 0.f) return false;
   if (!(L < INFINITY)) return true;
   const double px = R.q0.x, py = R.q0.y;
-  const double q = qmin_rect(R.q0.z, R.q0.w, R.q1.x, px - u1, px - u0,
-                             py - v1, py - v0);
+  const double q = qmin_rect(R.q0.z, R.q0.w, R.q1.x, sx, sy, px - u1,
+                             px - u0, py - v1, py - v0);
   return q <= (double)L * (1.0 + 1e-9) + 1e-6;
 }
 

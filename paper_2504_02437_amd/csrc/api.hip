@@ -148,7 +148,9 @@ static int make_layout(const gs_geometry* g, Layout& L, int& tx, int& ty) {
   L.ranges = take(tiles * 8);
   L.cursor = take(tiles * 4);
   L.tile_order = take(tiles * 4);
-  L.tile_loss = take(tiles * 16);
+  // A slot per 8x8 block where the compositing may take a tile in blocks.
+  const size_t blocks = g->tile < 32 ? (size_t)(g->tile / 8) * (g->tile / 8) : 1;
+  L.tile_loss = take(tiles * blocks * 16);
   const int ch = bin_chunk(tx, ty, g->n_views, g->capacity);
   L.chunk_counts = take(ch ? V * ((cap + ch - 1) / ch) * (size_t)tx * ty * 4 : 0);
   L.keys_unsorted = take(kc * 8);

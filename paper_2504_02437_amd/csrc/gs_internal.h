@@ -100,7 +100,7 @@ struct gs_workspace {
   uint32_t* cursor;      // [V * Ty * Tx] tile counts
   uint32_t* tile_order;  // [V * Ty * Tx] tiles by descending key count (the
                          // per-tile kernels take block b -> tile order[b])
-  double* tile_loss;     // [V * Ty * Tx][2] fused L1 loss and squared error
+  double* tile_loss;     // [V * Ty * Tx][2], or of each 8x8 block: fused L1 loss and squared error
                          // of each tile, summed by one small kernel
   uint32_t* chunk_counts;  // [V][chunks][Ty * Tx] keys of each chunk per
                            // tile, then each chunk's offset in the tile
@@ -189,8 +189,8 @@ hipError_t launch_render_bwd(gs_workspace* ws, const gs_settings* s,
                              int per_view_colour, const L1Fused* l1,
                              hipStream_t st, const PlanarJob* planar = nullptr,
                              bool window = false);
-hipError_t launch_l1_reduce(const gs_workspace* ws, double* loss,
-                            double* sqerr, hipStream_t st);
+hipError_t launch_l1_reduce(const gs_workspace* ws, const gs_settings* s,
+                            double* loss, double* sqerr, hipStream_t st);
 hipError_t launch_sh_colour(gs_workspace* ws, const gs_params* p,
                             const gs_camera* cams, hipStream_t st);
 hipError_t launch_sh_bwd(gs_workspace* ws, const gs_params* p,

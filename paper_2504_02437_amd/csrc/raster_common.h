@@ -73,23 +73,23 @@ __device__ __forceinline__ void stage(Entry& E, const Record& R,
 // to evaluate the staged entry: its footprint meets the render box rb and,
 // with the ellipse test, the ellipse q(d) <= L outside which no pixel is
 // admitted (admit.h).  Computed once per staged entry.
-template <int TILE, int NT>
+template <class Lay, int WAVES>
 __device__ inline int wave_mask(const Record& R, const int4& rb, int tu0,
                                 int tv0, float amin, bool ellipse) {
-  using Lay = PixLayout<TILE, NT>;
   float L = INFINITY;
   if (ellipse) {
     const int bu = __float_as_int(R.q2.z), bv = __float_as_int(R.q2.w);
     L = admit_level(R, bu & 0xffff, bu >> 16, bv & 0xffff, bv >> 16, amin);
   }
+  const double sx = -(double)R.q0.w / R.q0.z, sy = -(double)R.q0.w / R.q1.x;
   int m = 0;
 #pragma unroll
-  for (int w = 0; w < NT / 64; ++w) {
+  for (int w = 0; w < WAVES; ++w) {
     int wu, wv;
     Lay::wave_origin(w, wu, wv);
     const int u0 = max(rb.x, tu0 + wu), u1 = min(rb.y, tu0 + wu + Lay::WC - 1);
     const int v0 = max(rb.z, tv0 + wv), v1 = min(rb.w, tv0 + wv + Lay::FH - 1);
-    if (ellipse_meets(R, L, u0, u1, v0, v1)) m |= 1 << w;
+    if (ellipse_meets(R, L, sx, sy, u0, u1, v0, v1)) m |= 1 << w;
   }
   return m;
 }
@@ -146,7 +146,7 @@ __device__ inline int wave_bits(const Record& R, const int4& rb, int tu0,
                                 int tv0, int W, int H, float amin, float amax,
                                 bool ellipse) {
   using Lay = PixLayout<TILE, NT>;
-  const int m = wave_mask<TILE, NT>(R, rb, tu0, tv0, amin, ellipse);
+  const int m = wave_mask<Lay, NT / 64>(R, rb, tu0, tv0, amin, ellipse);
   const bool no_clamp = R.q1.y <= amax;
   int bits = 0;
 #pragma unroll
@@ -193,6 +193,104 @@ __device__ inline void publish_masks(WaveMasks<BATCH, NT>& m, int i0,
   }
 }
 
+// The split shape for few tiles: a workgroup of four waves per 8x8 block of
+// pixels, a wave per 4x4 footprint, and the four rows of a wave (16 lanes,
+// one per pixel) take four entries of the list side by side.  With one pixel
+// per lane and one entry at a time a wave spends 470 cycles on each entry of
+// its list, a chain of some sixty instructions, and while the tiles leave
+// SIMDs idle that chain is the time; here four entries share the step.
+// Forward / backward us at 80 tiles (160x120) 18.7 / 29.7 -> 9.4 / 15.2, at
+// 300 tiles (320x240) 28 / 47 -> 19 / 33 and 5 for k_spread.  Bound then by
+// staging (9 k of 22 k cycles: four loads one after the other, the ellipse
+// tests) and, at 300 tiles, by instruction issue.
+struct BlockLayout {
+  static constexpr int WC = 4, FH = 4, kSide = 8, kThreads = 256, kBatch = 256;
+  __device__ static void wave_origin(int w, int& wu, int& wv) {
+    wu = (w & 1) * WC;
+    wv = (w >> 1) * FH;
+  }
+};
+
+// Blocks of a tile.
+__host__ __device__ constexpr int tile_parts(int tile) {
+  return (tile / BlockLayout::kSide) * (tile / BlockLayout::kSide);
+}
+
+// The staged entries each wave of a block has to evaluate: bit masks, and the
+// same as a list.
+struct BlockLists {
+  uint64_t eval[4][BlockLayout::kBatch / 64];
+  uint16_t list[4][BlockLayout::kBatch];
+  // Called by every thread after it staged entry tid (m: its wave_mask).
+  __device__ __forceinline__ void publish(int m, int wave, int lane) {
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const uint64_t e = __builtin_amdgcn_ballot_w64((m >> w) & 1);
+      if (lane == 0) eval[w][wave] = e;
+    }
+  }
+  // The wave's list of the entries below jn, in order; returns their number.
+  __device__ __forceinline__ int gather(int jn, int wave, int lane) {
+    int n = 0;
+#pragma unroll
+    for (int c = 0; c < BlockLayout::kBatch / 64; ++c) {
+      const uint64_t v = eval[wave][c];
+      uint64_t e = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 |
+                   (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+      const int top = jn - 64 * c;
+      if (top < 64) e &= top <= 0 ? 0ull : (1ull << top) - 1;
+      if ((e >> lane) & 1)
+        list[wave][n + __builtin_amdgcn_mbcnt_hi((uint32_t)(e >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)e, 0u))] =
+            (uint16_t)(64 * c + lane);
+      n += __builtin_popcountll(e);
+    }
+    return n;
+  }
+};
+
+// The values of the lane's pixel in the wave's four rows.
+struct Rows {
+  float v[4];
+};
+
+__device__ __forceinline__ Rows all_rows(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  const auto a = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
+  return {{__uint_as_float(a[0]), __uint_as_float(a[1]), __uint_as_float(b[0]),
+           __uint_as_float(b[1])}};
+}
+
+// A lane's pixel and the words of the staged entries it reads.
+struct BlockPixel {
+  int u, v;
+  float uf, vf;
+};
+
+struct BlockWords {
+  float4 a, b;
+  float cb;
+  int4 box;
+  __device__ __forceinline__ void load(const Entry& E) {
+    a = E.a;
+    b = E.b;
+    cb = E.c.x;
+    box = E.box;
+  }
+};
+
+// Unclamped alpha o G of a pixel and its offsets, and whether the pixel lies
+// outside the render box (negative) or not.
+__device__ __forceinline__ float block_alpha(const BlockWords& w, const BlockPixel& px,
+                                             float& dx, float& dy, int& out) {
+  const Column col = column(w.a, w.b.y, px.uf);
+  dx = col.dx;
+  out = (px.u - w.box.x) | (w.box.y - px.u) | (px.v - w.box.z) | (w.box.w - px.v);
+  return alpha2(exponent2(col, w.a.y, w.b.x, px.vf, dy));
+}
+
 struct RasterArgs {
   const Record* rec;
   const int2* rbox;
@@ -215,8 +313,9 @@ __device__ __forceinline__ void tile_range(const RasterArgs& a, int t,
   e = min((long long)a.ranges[2 * t + 1], a.key_cap);
 }
 
-// Launch shape of the compositing kernels for the caller's settings; results
-// do not depend on it.
+// Launch shape of the compositing kernels for the caller's settings; the
+// decisions do not depend on it (nor on split_shape), sums only in the order
+// of their terms.
 //
 // Threads the caller leaves open, tile 16: four small footprints per tile
 // (256 threads, one pixel each) while the tiles alone leave SIMDs idle and
@@ -248,6 +347,25 @@ inline RasterShape raster_shape(const gs_workspace* ws, const gs_settings* s) {
                 : tiles >= 2048 ? 128 : 256;
   if (r.tile < 32 && r.batch > r.threads) r.batch = r.threads;
   return r;
+}
+
+// Whether the pass takes the split shape (BlockLayout): open threads, a tile
+// below 32 and few blocks.  Forward / backward us, one workgroup per tile
+// against blocks, gradients by the cheaper of planar rows and accumulators:
+//   tile 16: 80 tiles (160x120) 42 / 32, 37 / 25; 180 tiles 48 / 38, 40 / 33;
+//   300 tiles (320x240) 53 / 48, 47 / 47; 475 tiles 61 / 64, 62 / 75; 1,200
+//   tiles (640x480) 94 / 107, 111 / 161;
+//   tile 8: 300 tiles (160x120) 42 / 31, 38 / 25; 1,200 tiles (320x240) 58 /
+//   60, 51 / 46; 1,900 tiles 76 / 89, 73 / 74; 4,800 tiles 84 / 101, 94 / 109.
+// The backward of tile 8 gains for longer because a tile's own workgroup is a
+// single wave there.
+inline bool split_shape(const gs_workspace* ws, const gs_settings* s,
+                        bool backward) {
+  const int tile = ws->geo.tile;
+  if (s->block_threads != 0 || tile >= 32) return false;
+  const long long blocks = (long long)ws->geo.n_views * ws->tiles_x *
+                           ws->tiles_y * tile_parts(tile);
+  return blocks < (!backward ? 1900 : tile == 16 ? 1300 : 3000);
 }
 
 // Calls launcher.template go<TILE, BATCH, NT>() for a supported shape.

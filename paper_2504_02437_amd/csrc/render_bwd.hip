@@ -20,7 +20,7 @@
 // reduced over each 16-lane row with DPP (a transposed reduction that packs
 // four quantities into one register), merged across rows and waves by LDS
 // adds, and turned into the mean, conic and opacity gradients once per
-// entry and workgroup, which adds them to global memory (kSpreadPixels says
+// entry and workgroup, which adds them to global memory (kSpreadBlocks says
 // where).
 
 #include "raster_common.h"
@@ -284,6 +284,69 @@ __device__ __forceinline__ void walk_batch(
   }
 }
 
+// Adds the staged entries' gradients, from the nine sums of each, to global
+// memory.  Called by the NT threads of the workgroup after a barrier.
+template <int NT>
+__device__ __forceinline__ void flush(const BwdArgs& a, float (*acc)[9],
+                                      const Entry* ent, const float* eop,
+                                      const uint32_t* gid, int cnt, int k,
+                                      int tid) {
+  const RasterArgs& r = a.r;
+  float* gk = a.grad2d + (size_t)k * 5 * r.cap;
+  float* gc = a.grgb + (size_t)k * a.grgb_vstride;
+  // Per entry: the mean, conic and opacity gradients from the nine sums
+  // (A, B, C the unscaled conic, o the opacity), then one atomic each:
+  // straight into the planar gradients, or back into the entry's LDS slot
+  // for the per-Gaussian accumulators.
+  for (int jj = tid; jj < cnt; jj += NT) {
+    const float* ac = acc[jj];
+    const float s0 = ac[0], xs0 = ac[1], x2s0 = ac[2], s1 = ac[3];
+    const float xs1 = ac[4], s2 = ac[5];
+    const float4 ec = ent[jj].c;
+    const float A = ec.y, B = ec.z, C = ec.w;
+    float val[9];
+    val[0] = -fmaf(A, xs0, B * s1);   // dL/dpx
+    val[1] = -fmaf(C, s1, B * xs0);   // dL/dpy
+    val[2] = -0.5f * x2s0;            // dL/dA
+    val[3] = -xs1;                    // dL/dB
+    val[4] = -0.5f * s2;              // dL/dC
+    val[5] = s0 / eop[jj];            // dL/do
+    val[6] = ac[6];
+    val[7] = ac[7];
+    val[8] = ac[8];
+    if (a.gview) {
+      float* out = acc[jj];
+#pragma unroll
+      for (int q = 0; q < 5; ++q) out[q] = val[q];
+      out[5] = val[6]; out[6] = val[7]; out[7] = val[8]; out[8] = val[5];
+      continue;
+    }
+    const uint32_t g = gid[jj];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+      if (val[q] == 0.f) continue;
+      if (q < 5) atomicAdd(&gk[(size_t)q * r.cap + g], val[q]);
+      else if (q == 5) atomicAdd(&a.gop[g], val[q]);
+      else atomicAdd(&gc[(size_t)(q - 6) * r.cap + g], val[q]);
+    }
+  }
+  if (a.gview) {
+    // Nine consecutive lanes per entry: its adds fall in one 64-byte and
+    // one 32-byte piece, two requests to the memory side instead of nine.
+    __syncthreads();
+    double* gv = a.gview + (size_t)k * 8 * r.cap;
+    const float* flat = &acc[0][0];
+    for (int i = tid; i < cnt * 9; i += NT) {
+      const float val = flat[i];
+      if (val == 0.f) continue;
+      const int jj = i / 9, q = i - 9 * jj;
+      const size_t g = gid[jj];
+      const bool view = q < 5 || (q < 8 && a.view_colour);
+      atomicAdd(view ? gv + 8 * g + q : a.gsum + 4 * g + (q - 5), (double)val);
+    }
+  }
+}
+
 // The per-pixel work is predicated like the forward's: every lane evaluates
 // its pixels for each entry and the admit decision selects what is
 // accumulated.  A wave starts its backward walk at the largest n_last of its
@@ -398,9 +461,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(BG ? 1 : 5))
   const int maxlast = (int)min((long long)smax, e - s);
   const Record* rv = r.rec + (size_t)k * r.cap;
   const int2* rbv = r.rbox + (size_t)k * r.cap;
-  float* gk = a.grad2d + (size_t)k * 5 * r.cap;
-  float* gc = a.grgb + (size_t)k * a.grgb_vstride;
-
   for (int hi = maxlast; hi > 0; hi -= BATCH) {
     const int lo = max(0, hi - BATCH);
     const int cnt = hi - lo;
@@ -435,57 +495,214 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(BG ? 1 : 5))
                                              lane);
     }
     __syncthreads();
-    // Per entry: the mean, conic and opacity gradients from the nine sums
-    // (A, B, C the unscaled conic, o the opacity), then one atomic each:
-    // straight into the planar gradients, or back into the entry's LDS slot
-    // for the per-Gaussian accumulators.
-    for (int jj = tid; jj < cnt; jj += NT) {
-      const float* ac = acc[jj];
-      const float s0 = ac[0], xs0 = ac[1], x2s0 = ac[2], s1 = ac[3];
-      const float xs1 = ac[4], s2 = ac[5];
-      const float4 ec = ent[jj].c;
-      const float A = ec.y, B = ec.z, C = ec.w;
-      float val[9];
-      val[0] = -fmaf(A, xs0, B * s1);   // dL/dpx
-      val[1] = -fmaf(C, s1, B * xs0);   // dL/dpy
-      val[2] = -0.5f * x2s0;            // dL/dA
-      val[3] = -xs1;                    // dL/dB
-      val[4] = -0.5f * s2;              // dL/dC
-      val[5] = s0 / eop[jj];            // dL/do
-      val[6] = ac[6];
-      val[7] = ac[7];
-      val[8] = ac[8];
-      if (a.gview) {
-        float* out = acc[jj];
+    flush<NT>(a, acc, ent, eop, gid, cnt, k, tid);
+  }
+}
+
+// Sums over each 16-lane row of eight per-lane values: lane l of the row
+// receives the total of q[l >> 1] in the order 0, 4, 2, 6, 1, 5, 3, 7 (bit 3
+// of l picks the value's bit 0, bit 2 its bit 1, bit 1 its bit 2).  A
+// transposed reduction: each exchange merges two registers into one (see
+// wave_sum8 for bank_mask and the waits).
+__device__ __forceinline__ float merge8(float a, float b) {
+  float x;
+  asm("s_nop 1\n\t"
+      "v_add_f32_dpp %[x], %[a], %[a] row_shl:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %[x], %[b], %[b] row_shr:8 row_mask:0xf bank_mask:0xc\n\ts_nop 1"
+      : [x] "=&v"(x)
+      : [a] "v"(a), [b] "v"(b));
+  return x;
+}
+
+__device__ __forceinline__ float merge4(float a, float b) {
+  float x;
+  asm("s_nop 1\n\t"
+      "v_add_f32_dpp %[x], %[a], %[a] row_shl:4 row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %[x], %[b], %[b] row_shr:4 row_mask:0xf bank_mask:0xa\n\ts_nop 1"
+      : [x] "=&v"(x)
+      : [a] "v"(a), [b] "v"(b));
+  return x;
+}
+
+__device__ __forceinline__ float row_sum8(const float (&q)[8], int lane) {
+  const float a = merge4(merge8(q[0], q[1]), merge8(q[2], q[3]));
+  const float b = merge4(merge8(q[4], q[5]), merge8(q[6], q[7]));
+  const float a2 = add_dpp<0x4e>(a, a), b2 = add_dpp<0x4e>(b, b);
+  const float x = lane & 2 ? b2 : a2;
+  return add_dpp<0xb1>(x, x);
+}
+
+// The split shape (k_render_fwd_split): lane 16 r + p of a wave holds pixel p
+// and takes the entries n - 1 - 4 i - r of the wave's list.  A step evaluates
+// alpha, 1 / (1 - alpha) and the colour term of its own entry, hands them to
+// all rows, and every row runs the pixel's T and running colour sum through
+// the four entries in order, picking up the values that its own entry needs;
+// the nine sums are reduced within the row and added to the entry's LDS slot.
+template <int TILE, bool BG>
+__global__ __launch_bounds__(BlockLayout::kThreads)
+void k_render_bwd_split(BwdArgs a) {
+  constexpr int kBatch = BlockLayout::kBatch, NT = BlockLayout::kThreads;
+  __shared__ Entry ent[kBatch];
+  __shared__ float acc[kBatch][9];
+  __shared__ uint32_t gid[kBatch];
+  __shared__ float eop[kBatch];
+  __shared__ BlockLists lists;
+  __shared__ int wmax[4];
+  __shared__ double psh[NT / 64], lpart[2][NT / 64];
+  if ((int)blockIdx.x >= a.tile_blocks) {   // dispatched last: the tail
+    planar_part(a.planar, (int)blockIdx.x - a.tile_blocks,
+                (int)gridDim.x - a.tile_blocks, psh);
+    return;
+  }
+  const RasterArgs& r = a.r;
+  constexpr int kParts = tile_parts(TILE), kAcross = TILE / BlockLayout::kSide;
+  const int t = (int)r.order[blockIdx.x / kParts];
+  const int part = blockIdx.x % kParts;
+  const int tpv = r.Tx * r.Ty;
+  const int k = t / tpv;
+  const int rem = t - k * tpv;
+  const int ty = rem / r.Tx, tx = rem - ty * r.Tx;
+  const int tid = threadIdx.x, lane = tid & 63, row = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  long long s, e;
+  tile_range(r, t, s, e);
+  const size_t HW = (size_t)r.H * r.W;
+  const int bu = tx * TILE + (part % kAcross) * BlockLayout::kSide;
+  const int bv = ty * TILE + (part / kAcross) * BlockLayout::kSide;
+  int wu, wv;
+  BlockLayout::wave_origin(wave, wu, wv);
+  BlockPixel px;
+  px.u = bu + wu + (lane & 3);
+  px.v = bv + wv + ((lane >> 2) & 3);
+  px.uf = pinned((float)px.u);
+  px.vf = pinned((float)px.v);
+  const float amin = r.alpha_min;
+  // Pixels outside the image keep T = 0 and a zero gradient: every term they
+  // could add is zero.
+  float T = 0.f, g0 = 0.f, g1 = 0.f, g2 = 0.f, Sg = 0.f;
+  int last = 0;
+  float l1_abs = 0.f;
+  double l1_sq = 0.0;
+  if (px.u < r.W && px.v < r.H) {
+    const size_t pix = (size_t)px.v * r.W + px.u;
+    T = a.Tfin[(size_t)k * HW + pix];
+    last = a.nlast[(size_t)k * HW + pix];
+    const size_t i0 = (size_t)k * 3 * HW + pix;
+    if (a.target) {
+      float d[3];
 #pragma unroll
-        for (int q = 0; q < 5; ++q) out[q] = val[q];
-        out[5] = val[6]; out[6] = val[7]; out[7] = val[8]; out[8] = val[5];
-        continue;
+      for (int ch = 0; ch < 3; ++ch) {
+        d[ch] = a.rgb[i0 + ch * HW] - a.target[i0 + ch * HW];
+        if (row == 0) {   // one row adds the pixel's loss
+          l1_abs += fabsf(d[ch]);
+          l1_sq += (double)d[ch] * (double)d[ch];
+        }
       }
-      const uint32_t g = gid[jj];
+      g0 = l1_grad(d[0], a.l1_scale);
+      g1 = l1_grad(d[1], a.l1_scale);
+      g2 = l1_grad(d[2], a.l1_scale);
+    } else {
+      g0 = a.dL[i0];
+      g1 = a.dL[i0 + HW];
+      g2 = a.dL[i0 + 2 * HW];
+    }
+  }
+  const float Tb = T * (r.bg0 * g0 + r.bg1 * g1 + r.bg2 * g2);
+  if (a.target) {
+    double la = l1_abs, lq = l1_sq;
+    for (int off = 8; off > 0; off >>= 1) {
+      la += __shfl_down(la, off, 64);
+      lq += __shfl_down(lq, off, 64);
+    }
+    if (lane == 0) {
+      lpart[0][wave] = la;
+      lpart[1][wave] = lq;
+    }
+  }
+  const int wlast = __builtin_amdgcn_readfirstlane(wave_max(last));
+  if (lane == 0) wmax[wave] = wlast;
+  __syncthreads();
+  if (a.target && tid == 0) {
+    double* out = a.tile_loss + 2 * ((size_t)t * kParts + part);
+    out[0] = ((lpart[0][0] + lpart[0][1]) + (lpart[0][2] + lpart[0][3])) * a.l1_lam_inv;
+    out[1] = (lpart[1][0] + lpart[1][1]) + (lpart[1][2] + lpart[1][3]);
+  }
+  const int maxlast = (int)min((long long)max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3])),
+                               e - s);
+  const Record* rv = r.rec + (size_t)k * r.cap;
+  const int2* rbv = r.rbox + (size_t)k * r.cap;
+  // The value that the lane's row sum holds, and the slot that it adds it to
+  // (lane 1: the ninth sum).
+  const int slot = (lane & 15) == 1 ? 8
+                   : ((lane >> 3) & 1) | ((lane >> 2) & 1) << 1 | ((lane >> 1) & 1) << 2;
+  const bool adds = (lane & 1) == 0 || (lane & 15) == 1;
+  for (int hi = maxlast; hi > 0; hi -= kBatch) {
+    const int lo = max(0, hi - kBatch);
+    const int cnt = hi - lo;
+    __syncthreads();   // the previous batch is flushed
+    int m = 0, clampable = 0;
+    if (tid < cnt) {
+      const uint32_t g = r.vals[s + lo + tid];
+      gid[tid] = g;
+      const Record R = rv[g];
+      eop[tid] = R.q1.y;
+      const int4 box = unpack_box(rbv[g]);
+      stage(ent[tid], R, box, r.lop[g]);
+      m = wave_mask<BlockLayout, 4>(R, box, bu, bv, amin, r.ellipse_test);
+      clampable = R.q1.y > r.alpha_max;
+    }
+    lists.publish(m, wave, lane);
+    for (int i = tid; i < cnt * 9; i += NT) (&acc[0][0])[i] = 0.f;
+    const float amax = __syncthreads_or(clampable) ? r.alpha_max : INFINITY;
+    const int n = lists.gather(min(cnt, wlast - lo), wave, lane);
+    const uint16_t* list = lists.list[wave];
+    auto at = [&](int i) { return (int)list[max(n - 1 - 4 * i - row, 0)]; };
+    const int steps = (n + 3) >> 2;
+    if (steps > 0) {
+      int j = at(0), jn = at(1);
+      BlockWords w;
+      w.load(ent[j]);
+#pragma unroll 2
+      for (int i = 0; i < steps; ++i) {
+        BlockWords wn;
+        wn.load(ent[jn]);
+        const int jnn = at(i + 2);
+        float dx, dy;
+        int out;
+        const float oG = block_alpha(w, px, dx, dy, out);
+        const float al = fminf(amax, oG);
+        // Past the list's start the first entry stands again: not admitted.
+        out |= (last - 1 - lo - j) | (n - 1 - 4 * i - row);
+        const float alo = out >= 0 ? (al >= amin ? al : 0.f) : 0.f;
+        const float rom = __builtin_amdgcn_rcpf(1.f - alo);
+        const float cg = fmaf(w.b.z, g0, fmaf(w.b.w, g1, w.cb * g2));
+        const Rows xa = all_rows(alo), xr = all_rows(rom), xc = all_rows(cg);
+        float Town = 0.f, Sown = 0.f;
 #pragma unroll
-      for (int q = 0; q < 9; ++q) {
-        if (val[q] == 0.f) continue;
-        if (q < 5) atomicAdd(&gk[(size_t)q * r.cap + g], val[q]);
-        else if (q == 5) atomicAdd(&a.gop[g], val[q]);
-        else atomicAdd(&gc[(size_t)(q - 6) * r.cap + g], val[q]);
+        for (int q = 0; q < 4; ++q) {
+          T *= xr.v[q];
+          Town = q == 0 ? T : row == q ? T : Town;
+          Sown = q == 0 ? Sg : row == q ? Sg : Sown;
+          Sg = fmaf(xa.v[q], xc.v[q] - Sg, Sg);
+        }
+        const float wt = alo * Town, diff = cg - Sown;
+        float dpw = BG ? alo * fmaf(Town, diff, -(Tb * rom)) : wt * diff;
+        dpw = oG > amax ? 0.f : dpw;
+        const float xs0 = dx * dpw, s1 = dy * dpw;
+        const float q8[8] = {dpw, xs0, dx * xs0, s1, dx * s1, dy * s1, wt * g0, wt * g1};
+        const float x = row_sum8(q8, lane);
+        const float z = row_sum(wt * g2);
+        // Nothing is added for an entry that no pixel of the row admits.
+        const uint64_t hit = __builtin_amdgcn_ballot_w64(alo > 0.f);
+        const bool any = ((uint32_t)(hit >> (16 * row)) & 0xffffu) != 0;
+        if (any && adds) atomicAdd(&acc[j][slot], (lane & 15) == 1 ? z : x);
+        w = wn;
+        j = jn;
+        jn = jnn;
       }
     }
-    if (a.gview) {
-      // Nine consecutive lanes per entry: its adds fall in one 64-byte and
-      // one 32-byte piece, two requests to the memory side instead of nine.
-      __syncthreads();
-      double* gv = a.gview + (size_t)k * 8 * r.cap;
-      const float* flat = &acc[0][0];
-      for (int i = tid; i < cnt * 9; i += NT) {
-        const float val = flat[i];
-        if (val == 0.f) continue;
-        const int jj = i / 9, q = i - 9 * jj;
-        const size_t g = gid[jj];
-        const bool view = q < 5 || (q < 8 && a.view_colour);
-        atomicAdd(view ? gv + 8 * g + q : a.gsum + 4 * g + (q - 5), (double)val);
-      }
-    }
+    __syncthreads();
+    flush<NT>(a, acc, ent, eop, gid, cnt, k, tid);
   }
 }
 
@@ -542,12 +759,14 @@ __global__ __launch_bounds__(1024) void k_l1_reduce(L1ReduceJob j) {
 // entry points publish planar rows, so there a pass over the accumulators
 // follows (9 us at 300k Gaussians and one view), which pays at tiles below
 // 32 (1200x680, tile 16: 0.28 -> 0.164 ms with the pass; tile 32: 0.123 ms
-// either way) and images of this many pixels over all views (at 320x240 the
-// adds cost 2 us).  The accumulators are FP64: a Gaussian next to the camera
+// either way) from this many workgroups on.  Whole backward us, planar rows
+// against accumulators: 300 tiles of 16 48 / 52, 475 78 / 64, 690 106 / 82,
+// 1,200 123 / 107; 690 tiles of 8 49 / 46; in blocks, 320 25 / 27, 720 39 /
+// 33, 1,200 67 / 47.  The accumulators are FP64: a Gaussian next to the camera
 // sums thousands of tiles' parts that mostly cancel, and FP32 adds in
 // whatever order they arrive left its gradient 1.4e-6 to 4.6e-6 off from run
 // to run (now 4.0e-7 on the same input, every run).
-constexpr long long kSpreadPixels = 400000;
+constexpr int kSpreadBlocks = 450;
 
 struct BwdLauncher {
   const BwdArgs& a;
@@ -562,6 +781,13 @@ struct BwdLauncher {
     else
       hipLaunchKernelGGL((k_render_bwd<T, B, N, false>), dim3(blocks),
                          dim3(N), 0, st, a);
+  }
+  void split(int tile) const {
+    const dim3 grid(blocks), nt(BlockLayout::kThreads);
+    if (tile == 8 && bg) hipLaunchKernelGGL((k_render_bwd_split<8, true>), grid, nt, 0, st, a);
+    else if (tile == 8) hipLaunchKernelGGL((k_render_bwd_split<8, false>), grid, nt, 0, st, a);
+    else if (bg) hipLaunchKernelGGL((k_render_bwd_split<16, true>), grid, nt, 0, st, a);
+    else hipLaunchKernelGGL((k_render_bwd_split<16, false>), grid, nt, 0, st, a);
   }
 };
 
@@ -587,15 +813,14 @@ hipError_t launch_render_bwd(gs_workspace* ws, const gs_settings* s,
   a.grad2d = ws->grad2d; a.gop = ws->gop;
   a.grgb = per_view_colour ? ws->gcol : grad_rgb;
   a.grgb_vstride = per_view_colour ? (size_t)3 * ws->geo.capacity : 0;
-  const long long pixels =
-      (long long)ws->geo.n_views * ws->geo.width * ws->geo.height;
-  const bool spread =
-      !window && ws->geo.tile < 32 && pixels >= kSpreadPixels;
-  const bool acc = window || spread;
-  a.gview = acc ? ws->gview : nullptr; a.gsum = acc ? ws->gsum : nullptr;
   a.view_colour = per_view_colour;
   const int tiles = ws->geo.n_views * ws->tiles_x * ws->tiles_y;
-  a.tile_blocks = tiles;
+  const bool split = split_shape(ws, s, true);
+  a.tile_blocks = split ? tiles * tile_parts(ws->geo.tile) : tiles;
+  const bool spread =
+      !window && ws->geo.tile < 32 && a.tile_blocks >= kSpreadBlocks;
+  const bool acc = window || spread;
+  a.gview = acc ? ws->gview : nullptr; a.gsum = acc ? ws->gsum : nullptr;
   a.planar = planar ? *planar : PlanarJob{};
   if (tiles <= 0) {
     if (planar) {
@@ -606,10 +831,12 @@ hipError_t launch_render_bwd(gs_workspace* ws, const gs_settings* s,
     // The regulariser's workgroups (a grid stride over the Gaussians, as
     // many as its own launch would have) follow the tiles'.
     const RasterShape shape = raster_shape(ws, s);
-    const int nt = shape.threads;
+    const int nt = split ? BlockLayout::kThreads : shape.threads;
     const int pb = planar ? min(256, (planar->cap + nt - 1) / nt) : 0;
     const bool bg = s->bg[0] != 0.f || s->bg[1] != 0.f || s->bg[2] != 0.f;
-    dispatch_shape(shape, BwdLauncher{a, tiles + pb, bg, st});
+    const BwdLauncher launcher{a, a.tile_blocks + pb, bg, st};
+    if (split) launcher.split(shape.tile);
+    else dispatch_shape(shape, launcher);
     if (spread && ws->geo.capacity > 0) {
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
@@ -620,20 +847,22 @@ hipError_t launch_render_bwd(gs_workspace* ws, const gs_settings* s,
   if (l1 && !l1->defer_reduce) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_l1_reduce(ws, l1->loss, l1->sqerr, st);
+    return launch_l1_reduce(ws, s, l1->loss, l1->sqerr, st);
   }
   return hipGetLastError();
 }
 
-L1ReduceJob l1_reduce_job(const gs_workspace* ws, double* loss, double* sqerr) {
+L1ReduceJob l1_reduce_job(const gs_workspace* ws, const gs_settings* s,
+                          double* loss, double* sqerr) {
+  const int parts = split_shape(ws, s, true) ? tile_parts(ws->geo.tile) : 1;
   return L1ReduceJob{(const double2*)ws->tile_loss, ws->geo.n_views,
-                     ws->tiles_x * ws->tiles_y, loss, sqerr};
+                     ws->tiles_x * ws->tiles_y * parts, loss, sqerr};
 }
 
-hipError_t launch_l1_reduce(const gs_workspace* ws, double* loss,
-                            double* sqerr, hipStream_t st) {
+hipError_t launch_l1_reduce(const gs_workspace* ws, const gs_settings* s,
+                            double* loss, double* sqerr, hipStream_t st) {
   hipLaunchKernelGGL(k_l1_reduce, dim3(1), dim3(1024), 0, st,
-                     l1_reduce_job(ws, loss, sqerr));
+                     l1_reduce_job(ws, s, loss, sqerr));
   return hipGetLastError();
 }
 

@@ -302,6 +302,131 @@ __global__ __launch_bounds__(NT) void k_render_fwd(FwdArgs a) {
   }
 }
 
+// The split shape: grid (tiles * blocks of a tile); lane 16 r + p of a wave
+// holds pixel p and takes the entries 4 i + r of the wave's list.  A step
+// evaluates alpha of its own entry, hands the four alphas of the pixel to all
+// rows (an entry that does not admit the pixel as 0, which leaves T as it
+// is), and every row runs the pixel's transmittance through the four in
+// order, with the same operations as k_render_fwd, so that T, the decisions
+// and n_last are the same to the bit; the colour is summed per row and joined
+// at the end.
+template <int TILE>
+__global__ __launch_bounds__(BlockLayout::kThreads)
+void k_render_fwd_split(FwdArgs a) {
+  constexpr int kBatch = BlockLayout::kBatch;
+  __shared__ Entry ent[kBatch];
+  __shared__ BlockLists lists;
+  const RasterArgs& r = a.r;
+  constexpr int kParts = tile_parts(TILE), kAcross = TILE / BlockLayout::kSide;
+  const int t = (int)r.order[blockIdx.x / kParts];
+  const int part = blockIdx.x % kParts;
+  const int tpv = r.Tx * r.Ty;
+  const int k = t / tpv;
+  const int rem = t - k * tpv;
+  const int ty = rem / r.Tx, tx = rem - ty * r.Tx;
+  const int tid = threadIdx.x, lane = tid & 63, row = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  long long s, e;
+  tile_range(r, t, s, e);
+  const int bu = tx * TILE + (part % kAcross) * BlockLayout::kSide;
+  const int bv = ty * TILE + (part / kAcross) * BlockLayout::kSide;
+  int wu, wv;
+  BlockLayout::wave_origin(wave, wu, wv);
+  BlockPixel px;
+  px.u = bu + wu + (lane & 3);
+  px.v = bv + wv + ((lane >> 2) & 3);
+  px.uf = pinned((float)px.u);
+  px.vf = pinned((float)px.v);
+  const bool image = px.u < r.W && px.v < r.H;
+  const float amin = r.alpha_min, tmin = r.T_min;
+  float T = image ? 1.f : -1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
+  int last = 0;
+  const Record* rv = r.rec + (size_t)k * r.cap;
+  const int2* rbv = r.rbox + (size_t)k * r.cap;
+  for (long long b0 = s; b0 < e; b0 += kBatch) {
+    if (__syncthreads_or(T > 0.f) == 0) break;
+    const int cnt = (int)min((long long)kBatch, e - b0);
+    int m = 0, clampable = 0;
+    if (tid < cnt) {
+      const uint32_t g = r.vals[b0 + tid];
+      const Record R = rv[g];
+      const int4 box = unpack_box(rbv[g]);
+      stage(ent[tid], R, box, r.lop[g]);
+      m = wave_mask<BlockLayout, 4>(R, box, bu, bv, amin, r.ellipse_test);
+      clampable = R.q1.y > r.alpha_max;
+    }
+    lists.publish(m, wave, lane);
+    const float amax = __syncthreads_or(clampable) ? r.alpha_max : INFINITY;
+    const int base = (int)(b0 - s) + 1;
+    const int n = lists.gather(cnt, wave, lane);
+    if (n == 0) continue;
+    // The entry of the step after next and the words of the next are read
+    // while this step is computed.
+    const uint16_t* list = lists.list[wave];
+    auto at = [&](int i) { return (int)list[min(4 * i + row, n - 1)]; };
+    const int steps = (n + 3) >> 2;
+    int j = at(0), jn = at(1);
+    BlockWords w;
+    w.load(ent[j]);
+#pragma unroll 2
+    for (int i = 0; i < steps; ++i) {
+      if (__builtin_amdgcn_ballot_w64(T > 0.f) == 0) break;
+      BlockWords wn;
+      wn.load(ent[jn]);
+      const int jnn = at(i + 2);
+      float dx, dy;
+      int out;
+      const float oG = block_alpha(w, px, dx, dy, out);
+      const float al0 = fminf(amax, oG);
+      // Past the list's end the last entry stands again: not admitted.
+      out |= n - 1 - 4 * i - row;
+      const float al = out >= 0 ? (al0 >= amin ? al0 : 0.f) : 0.f;
+      const Rows x = all_rows(al);
+      float Town = T;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (q) Town = row == q ? T : Town;
+        const float Tn = fmaf(-x.v[q], T, T);
+        T = Tn >= tmin ? Tn : -fabsf(T);
+      }
+      const float Tn = fmaf(-al, Town, Town);
+      const bool con = Tn >= tmin;
+      const float wt = con ? al * Town : 0.f;
+      C0 = fmaf(w.b.z, wt, C0);
+      C1 = fmaf(w.b.w, wt, C1);
+      C2 = fmaf(w.cb, wt, C2);
+      const int idx = al > 0.f ? base + j : 0;
+      last = con ? max(last, idx) : last;
+      w = wn;
+      j = jn;
+      jn = jnn;
+    }
+  }
+  // Sums over the rows, in every row.
+  auto joined = [](float x) {
+    const Rows v = all_rows(x);
+    return (v.v[0] + v.v[1]) + (v.v[2] + v.v[3]);
+  };
+  C0 = joined(C0);
+  C1 = joined(C1);
+  C2 = joined(C2);
+  const Rows l = all_rows(__int_as_float(last));
+#pragma unroll
+  for (int q = 0; q < 4; ++q) last = max(last, __float_as_int(l.v[q]));
+  if (!image) return;
+  const float Tf = fabsf(T);
+  const size_t HW = (size_t)r.H * r.W;
+  const size_t pix = (size_t)px.v * r.W + px.u;
+  if (row < 3) {   // a row per channel
+    const float bg = row == 0 ? r.bg0 : row == 1 ? r.bg1 : r.bg2;
+    const float c = row == 0 ? C0 : row == 1 ? C1 : C2;
+    a.rgb[((size_t)k * 3 + row) * HW + pix] = fmaf(Tf, bg, c);
+  } else {
+    a.T[(size_t)k * HW + pix] = Tf;
+    a.nlast[(size_t)k * HW + pix] = last;
+  }
+}
+
 template <int MODE>
 struct FwdLauncher {
   const FwdArgs& a;
@@ -339,8 +464,14 @@ hipError_t launch_render_fwd(gs_workspace* ws, const gs_settings* s,
   a.rgb = rgb; a.T = T; a.nlast = nlast; a.dom = nullptr; a.counts = nullptr;
   const int blocks = ws->geo.n_views * ws->tiles_x * ws->tiles_y;
   if (blocks <= 0) return hipSuccess;
-  dispatch_shape(raster_shape(ws, s),
-                 FwdLauncher<kRender>{a, blocks, st});
+  if (split_shape(ws, s, false)) {
+    const int tile = ws->geo.tile;
+    const dim3 grid(blocks * tile_parts(tile)), nt(BlockLayout::kThreads);
+    if (tile == 8) hipLaunchKernelGGL(k_render_fwd_split<8>, grid, nt, 0, st, a);
+    else hipLaunchKernelGGL(k_render_fwd_split<16>, grid, nt, 0, st, a);
+    return hipGetLastError();
+  }
+  dispatch_shape(raster_shape(ws, s), FwdLauncher<kRender>{a, blocks, st});
   return hipGetLastError();
 }
 

@@ -68,7 +68,8 @@ struct L1ReduceJob {
   double* sqerr;         // [V], accumulated; may be null
 };
 
-L1ReduceJob l1_reduce_job(const gs_workspace* ws, double* loss, double* sqerr);
+L1ReduceJob l1_reduce_job(const gs_workspace* ws, const gs_settings* s,
+                          double* loss, double* sqerr);
 
 // One workgroup (a multiple of 64 threads): wave w sums the views w,
 // w + waves, ..., each over its tiles in a fixed lane order and shuffle

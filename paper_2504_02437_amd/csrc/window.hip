@@ -142,7 +142,8 @@ int enqueue_iteration(const gs_window_desc* d, hipStream_t st) {
                                   d->sqerr_dev, st, reg ? &planar : nullptr,
                                   true)))
     return rc;
-  const L1ReduceJob l1 = l1_reduce_job(d->ws, d->loss_dev, d->sqerr_dev);
+  const L1ReduceJob l1 = l1_reduce_job(d->ws, &d->settings, d->loss_dev,
+                                       d->sqerr_dev);
   // The camera constants were formed by the clearing launch, the gradients
   // are in the per-Gaussian accumulators.
   if ((rc = project_bwd_checked(d->ws, &params, d->cams, &grad, st, &l1,
