@@ -85,10 +85,22 @@ __device__ inline void l1_reduce_part(const L1ReduceJob& j, double* part) {
     const int k = k0 + w;
     if (k < j.V) {
       double la = 0.0, lq = 0.0;
-      for (int i = lane; i < j.tpv; i += 64) {
-        const double2 q = j.tile_loss[(size_t)k * j.tpv + i];
-        la += q.x;
-        lq += q.y;
+      // Eight loads in flight, added in order (one wave sums a view, and one
+      // load at a time is a memory latency per 64 tiles: 3,225 tiles 14 us,
+      // with eight 6.5).
+      const double2* t = j.tile_loss + (size_t)k * j.tpv;
+      for (int i0 = lane; i0 < j.tpv; i0 += 8 * 64) {
+        double2 q[8];
+#pragma unroll
+        for (int n = 0; n < 8; ++n) {
+          const int i = i0 + 64 * n;
+          q[n] = i < j.tpv ? t[i] : make_double2(0.0, 0.0);
+        }
+#pragma unroll
+        for (int n = 0; n < 8; ++n) {
+          la += q[n].x;
+          lq += q[n].y;
+        }
       }
       for (int off = 32; off > 0; off >>= 1) {
         la += __shfl_down(la, off, 64);
