@@ -90,34 +90,57 @@ __device__ __forceinline__ float fold16(float a, float b) {
   return __uint_as_float(t[0]) + __uint_as_float(t[1]);
 }
 
-// Sum over the wave of eight per-lane values: lane 8k receives the total of
-// q[k].  A transposed reduction: the two half-wave folds and the two row
-// folds leave two registers whose row r holds one value's 16 row partials
-// (value r of the first four, in the order 0, 2, 4, 6 / 1, 3, 5, 7 below),
-// a shift-8 exchange writing only banks 0-1 from the first register and
-// banks 2-3 from the second (bank_mask: no select) merges them, and three
-// shifts within each half-row finish the sums.  The DPP adds read
-// registers written just before them, which needs two wait states after a
-// VALU write (the s_nop 1 before each); lanes whose DPP source lies outside
-// their row are not written and are not used.  Runs in converged control
-// flow with every lane active.
-__device__ __forceinline__ float wave_sum8(const float (&q)[8]) {
-  const float r1 = fold16(fold32(q[0], q[4]), fold32(q[2], q[6]));
-  const float r2 = fold16(fold32(q[1], q[5]), fold32(q[3], q[7]));
-  float x;
+// Sums over the wave of the nine values S0, dx S0, dx^2 S0, S1, dx S1, S2, r,
+// g and b.  A transposed reduction: lanes 16 apart share their image column
+// and so dx, hence the six values are folded over the four rows of lanes
+// first, two or four to a register, and only their column sums are multiplied
+// by dx.  That leaves four registers, A with S0, S2, S1, r in the rows 0-3, dx
+// A, dx^2 A and B with g in the rows 0 and 1 and b in 2 and 3 (not folded
+// further: the LDS adds join them).  Shift-8 and shift-4 exchanges that write
+// only some banks (bank_mask: no select) merge the four into one, a quad of
+// lanes per register in the order A, dx^2 A, dx A, B, and two exchanges
+// within the quad finish the sums: every lane of a quad holds its total
+// (nine_slot says which one).  DPP adds need two wait states after the VALU
+// write of what they read.  Runs in converged control flow with every lane
+// active.  Against sums of all nine per lane and two LDS adds (some forty
+// instructions per entry and wave, beside about 25 per pixel): 10 views
+// 1200x680, tile 32, 728 -> 688 us; one view, tile 16, 138 -> 128 us.
+__device__ __forceinline__ float wave_sum9(float S0, float S1, float S2,
+                                           float d_r, float d_g, float d_b,
+                                           float dx) {
+  const float A = fold16(fold32(S0, S1), fold32(S2, d_r));
+  const float B = fold32(d_g, d_b);
+  const float A1 = dx * A, A2 = dx * A1;
+  float x, y, z;
   asm volatile(
       "s_nop 1\n\t"
-      "v_add_f32_dpp %[x], %[r1], %[r1] row_shl:8 row_mask:0xf bank_mask:0x3\n\t"
-      "v_add_f32_dpp %[x], %[r2], %[r2] row_shr:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %[x], %[A], %[A] row_shl:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %[x], %[A1], %[A1] row_shr:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %[y], %[A2], %[A2] row_shl:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %[y], %[B], %[B] row_shr:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %[z], %[x], %[x] row_shl:4 row_mask:0xf bank_mask:0x5\n\t"
+      "s_nop 0\n\t"
+      "v_add_f32_dpp %[z], %[y], %[y] row_shr:4 row_mask:0xf bank_mask:0xa\n\t"
       "s_nop 1\n\t"
-      "v_add_f32_dpp %[x], %[x], %[x] row_shl:4 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %[z], %[z], %[z] quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
       "s_nop 1\n\t"
-      "v_add_f32_dpp %[x], %[x], %[x] row_shl:2 row_mask:0xf bank_mask:0xf\n\t"
-      "s_nop 1\n\t"
-      "v_add_f32_dpp %[x], %[x], %[x] row_shl:1 row_mask:0xf bank_mask:0xf"
-      : [x] "=&v"(x)
-      : [r1] "v"(r1), [r2] "v"(r2));
-  return x;
+      "v_add_f32_dpp %[z], %[z], %[z] quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+      : [x] "=&v"(x), [y] "=&v"(y), [z] "=&v"(z)
+      : [A] "v"(A), [A1] "v"(A1), [A2] "v"(A2), [B] "v"(B));
+  return z;
+}
+
+// The slot of the nine (in the order above) that a lane adds its wave_sum9
+// to, -1 for none: the first lane of each quad that holds one.
+__device__ __forceinline__ int nine_slot(int lane) {
+  if (lane & 3) return -1;
+  const int row = lane >> 4;
+  switch ((lane >> 2) & 3) {
+    case 0: return row == 0 ? 0 : row == 1 ? 5 : row == 2 ? 3 : 6;   // A
+    case 1: return row == 0 ? 2 : -1;                                // dx^2 A
+    case 2: return row == 0 ? 1 : row == 2 ? 4 : -1;                 // dx A
+    default: return row < 2 ? 7 : 8;                                 // B
+  }
 }
 
 // Sum over the lane's 16-lane row, in every lane of the row.
@@ -220,7 +243,7 @@ template <bool CLAMP, bool BG, int TILE, int NT>
 __device__ __forceinline__ void walk_entry(
     BwdPix<PixLayout<TILE, NT>::PPT>& px, const Entry* ent, float (*acc)[9],
     int j, int pos, bool fast, int u, int v0, float uf, float amin,
-    float amax, int lane) {
+    float amax, int slot) {
   constexpr int PPT = PixLayout<TILE, NT>::PPT;
   const float4 ea = ent[j].a;
   const float4 eb = ent[j].b;
@@ -244,18 +267,11 @@ __device__ __forceinline__ void walk_entry(
   const EntrySums es = entry_bwd<CLAMP, BG>(px, col, ea.y, eb.x, eb.z, eb.w,
                                             ecb, amin, amax, inb);
   if (__builtin_amdgcn_ballot_w64(es.hit) != 0) {
-    // Wave totals of eight of the nine per-lane sums, added into the
-    // entry's LDS slot by lanes 0, 8, ..., 56 (distinct addresses), and row
-    // totals of the ninth by lane 0 of each row; the other waves of the
-    // tile meet in the LDS adds.
-    const float dx = col.dx, dxS0 = dx * es.S0;
-    const float q[8] = {es.S0, dxS0, dx * dxS0, es.S1,
-                        dx * es.S1, es.S2, es.d_r, es.d_g};
-    const float x = wave_sum8(q);
-    const float z = row_sum(es.d_b);
-    float* ac = acc[j];
-    if ((lane & 7) == 0) atomicAdd(&ac[lane >> 3], x);
-    if ((lane & 15) == 0) atomicAdd(&ac[8], z);
+    // The wave totals, added into the entry's LDS slots in one instruction;
+    // the other waves of the tile meet there.
+    const float x = wave_sum9(es.S0, es.S1, es.S2, es.d_r, es.d_g, es.d_b,
+                              col.dx);
+    if (slot >= 0) atomicAdd(&acc[j][slot], x);
   }
 }
 
@@ -266,7 +282,7 @@ __device__ __forceinline__ void walk_batch(
     BwdPix<PixLayout<TILE, NT>::PPT>& px, const Entry* ent,
     const WaveMasks<BATCH, NT>& masks, float (*acc)[9], int jn, int lo,
     int wave, int wfirst, int u, int v0, float uf, float amin, float amax,
-    int lane) {
+    int slot) {
   for (int k = (jn - 1) >> 5; k >= 0; --k) {
     uint32_t e = __builtin_amdgcn_readfirstlane(masks.eval[wave][k]);
     const uint32_t f = __builtin_amdgcn_readfirstlane(masks.fast[wave][k]);
@@ -279,7 +295,7 @@ __device__ __forceinline__ void walk_batch(
       const int pos = lo + j;
       walk_entry<CLAMP, BG, TILE, NT>(px, ent, acc, j, pos,
                                       ((f >> b) & 1) && pos < wfirst, u, v0,
-                                      uf, amin, amax, lane);
+                                      uf, amin, amax, slot);
     }
   }
 }
@@ -389,6 +405,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(BG ? 1 : 5))
   __shared__ WaveMasks<BATCH, NT> masks;
   const float uf = pinned((float)u);
   const float amax = r.alpha_max, amin = r.alpha_min;
+  const int slot = nine_slot(lane);
   BwdPix<PPT> px;
   int mylast = 0, myfirst = 0x7fffffff;
   float l1_abs = 0.f;
@@ -488,11 +505,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(BG ? 1 : 5))
     if (__syncthreads_or(clampable)) {
       walk_batch<true, BG, TILE, BATCH, NT>(px, ent, masks, acc, jn, lo, wave,
                                             wfirst, u, v0, uf, amin, amax,
-                                            lane);
+                                            slot);
     } else {
       walk_batch<false, BG, TILE, BATCH, NT>(px, ent, masks, acc, jn, lo, wave,
                                              wfirst, u, v0, uf, amin, amax,
-                                             lane);
+                                             slot);
     }
     __syncthreads();
     flush<NT>(a, acc, ent, eop, gid, cnt, k, tid);
@@ -503,7 +520,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(BG ? 1 : 5))
 // receives the total of q[l >> 1] in the order 0, 4, 2, 6, 1, 5, 3, 7 (bit 3
 // of l picks the value's bit 0, bit 2 its bit 1, bit 1 its bit 2).  A
 // transposed reduction: each exchange merges two registers into one (see
-// wave_sum8 for bank_mask and the waits).
+// wave_sum9 for bank_mask and the waits).
 __device__ __forceinline__ float merge8(float a, float b) {
   float x;
   asm("s_nop 1\n\t"
