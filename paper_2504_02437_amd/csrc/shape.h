@@ -71,6 +71,12 @@ struct ShapeJob {
 
 ShapeJob shape_job(const gs_workspace* ws, const gs_params* p);
 
+// The opacity of a logit and its base-2 logarithm.
+__device__ inline void shape_opacity(float logit, float& op, float& lop) {
+  op = (float)(1.0 / (1.0 + exp(-(double)logit)));
+  lop = (float)log2((double)op);
+}
+
 // Gaussian g (any g: those past the live count do nothing).
 __device__ inline void shape_one(const ShapeJob& j, int g) {
   const int n = min(*j.n_dev, j.cap);
@@ -82,9 +88,7 @@ __device__ inline void shape_one(const ShapeJob& j, int g) {
   // A failed shape (zero or non-finite quaternion, non-finite scale) is
   // culled in every view; a valid one has a finite, non-negative Sigma_00.
   if (!S.ok) j.sig[g] = NAN;
-  const float op = (float)(1.0 / (1.0 + exp(-(double)j.opl[g])));
-  j.op[g] = op;
-  j.lop[g] = (float)log2((double)op);
+  shape_opacity(j.opl[g], j.op[g], j.lop[g]);
 }
 
 // FP64 camera constants of the projection and its backward, kCamDoubles
