@@ -382,6 +382,57 @@ __global__ __launch_bounds__(1024) void k_chunk_scan(ChunkScanArgs a) {
   }
 }
 
+// k_chunk_scan and k_tile_ranges of one view in one workgroup, a thread per
+// tile: for grids of at most 1,024 tiles and 64 chunks, where each of the two
+// is a launch of 4 us that waits for memory.  320x240, 30k Gaussians (59
+// chunks) 4.6 + 3.8 us, now 5.4; 160x120, 10k (20 chunks) 4.0 + 3.7, now 3.1.
+constexpr int kSmallTiles = 1024, kSmallChunks = 64;
+
+__global__ __launch_bounds__(kSmallTiles)
+void k_small_ranges(ChunkScanArgs a, RangeArgs ra) {
+  __shared__ uint32_t wsum[kSmallTiles / 64];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  uint32_t run = 0;
+  if (t < a.tiles) {
+    uint32_t* C = a.chunk_counts + t;
+    constexpr int kAhead = 32;
+    for (int c0 = 0; c0 < a.chunks; c0 += kAhead) {
+      uint32_t v[kAhead];
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j)
+        v[j] = c0 + j < a.chunks ? C[(size_t)(c0 + j) * a.tiles] : 0u;
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) {
+        if (c0 + j < a.chunks) C[(size_t)(c0 + j) * a.tiles] = run;
+        run += v[j];
+      }
+    }
+    a.counts[t] = run;
+  }
+  // 64 chunks of at most 2,048 Gaussians in 1,024 tiles each: 32 bits hold it.
+  uint32_t incl = run;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t y = __shfl_up(incl, off, 64);
+    if (lane >= off) incl += y;
+  }
+  if (lane == 63) wsum[w] = incl;
+  __syncthreads();
+  uint32_t before = 0, total = 0;
+#pragma unroll
+  for (int i = 0; i < kSmallTiles / 64; ++i) {
+    if (i < w) before += wsum[i];
+    total += wsum[i];
+  }
+  if (t < a.tiles) {
+    ra.ranges[2 * t] = before + incl - run;
+    ra.ranges[2 * t + 1] = before + incl;
+  }
+  if (t == 0) {
+    ra.ctr->n_keys = total;
+    if (total > ra.key_cap) atomicOr(&ra.ctr->status, GS_STATUS_KEY_OVERFLOW);
+  }
+}
+
 template <int NT>
 __device__ void order_tiles(const uint32_t* ranges, uint32_t* order, int n,
                             uint32_t* cnt, uint32_t* wsum, uint32_t* mm);
@@ -599,9 +650,13 @@ hipError_t launch_chunked(const ScatterArgs& c, const RangeArgs& ra,
   ChunkScanArgs sa;
   sa.chunk_counts = c.chunk_counts; sa.counts = counts;
   sa.tiles = nb; sa.chunks = nch;
-  hipLaunchKernelGGL(k_chunk_scan, dim3((nb + 63) / 64, V), dim3(1024), 0, st,
-                     sa);
-  hipLaunchKernelGGL(k_tile_ranges, dim3(V), dim3(kScanThreads), 0, st, ra);
+  if (V == 1 && nb <= kSmallTiles && nch <= kSmallChunks) {
+    hipLaunchKernelGGL(k_small_ranges, dim3(1), dim3(kSmallTiles), 0, st, sa, ra);
+  } else {
+    hipLaunchKernelGGL(k_chunk_scan, dim3((nb + 63) / 64, V), dim3(1024), 0, st,
+                       sa);
+    hipLaunchKernelGGL(k_tile_ranges, dim3(V), dim3(kScanThreads), 0, st, ra);
+  }
   ScatterArgs cs = c;
   cs.nch = nch;
   const int n = V * nb;
