@@ -505,6 +505,27 @@ GS_API int gs_mlp_adam(float* weights, const float* dweights, float* adam_m,
                        float* adam_v, float lr, float beta1, float beta2,
                        float eps, int32_t step, void* stream);
 
+/* Forward pass with the features normalised, (x - x_mean) / x_dev, and the
+ * outputs brought back, y y_dev + y_mean, in one launch: x [m][32] -> y
+ * [m][7]; x_mean, x_dev [32], y_mean, y_dev [7]. */
+GS_API int gs_mlp_predict(const float* weights, const float* x, int32_t m,
+                          const float* x_mean, const float* x_dev,
+                          const float* y_mean, const float* y_dev, float* y,
+                          void* stream);
+
+/* One Adam step on the mean squared error of the normalised targets
+ * (gs_mlp_fwd, gs_mlp_mse, gs_mlp_bwd and gs_mlp_adam on normalised features
+ * and targets): 1 <= m < 2^24 rows.  WRITES the loss and dweights.
+ *   scratch  device float [m * (128 + 7 + 7)], caller-owned, overwritten */
+GS_API int gs_mlp_train_step(float* weights, const float* x,
+                             const float* target, int32_t m,
+                             const float* x_mean, const float* x_dev,
+                             const float* y_mean, const float* y_dev,
+                             float* scratch, double* loss_dev, float* dweights,
+                             float* adam_m, float* adam_v, float lr,
+                             float beta1, float beta2, float eps, int32_t step,
+                             void* stream);
+
 /* ---- One mapping iteration of a keyframe window as a HIP graph ----
  *
  * The map optimisation (Methodology: Map Optimization with Planar

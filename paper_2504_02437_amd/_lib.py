@@ -140,6 +140,12 @@ _SIGS = {
     "gs_mlp_bwd": (C.c_int, [_vp, _vp, _vp, _vp, C.c_int32, _vp, _vp]),
     "gs_mlp_adam": (C.c_int, [_vp, _vp, _vp, _vp, C.c_float, C.c_float,
                               C.c_float, C.c_float, C.c_int32, _vp]),
+    "gs_mlp_predict": (C.c_int, [_vp, _vp, C.c_int32, _vp, _vp, _vp, _vp, _vp,
+                                 _vp]),
+    "gs_mlp_train_step": (C.c_int, [_vp, _vp, _vp, C.c_int32, _vp, _vp, _vp,
+                                    _vp, _vp, _vp, _vp, _vp, _vp, C.c_float,
+                                    C.c_float, C.c_float, C.c_float, C.c_int32,
+                                    _vp]),
     "gs_read_status": (C.c_int, [_vp, _vp, _P(C.c_int32), _P(C.c_int64),
                                  C.c_int32]),
     "gs_window_build": (C.c_int, [_P(gs_window_desc), _vp, _P(_vp)]),

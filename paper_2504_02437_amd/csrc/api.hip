@@ -736,6 +736,36 @@ int gs_mlp_adam(float* weights, const float* dweights, float* adam_m,
                                 eps, step, (hipStream_t)stream), "mlp_adam");
 }
 
+int gs_mlp_predict(const float* weights, const float* x, int32_t m,
+                   const float* x_mean, const float* x_dev,
+                   const float* y_mean, const float* y_dev, float* y,
+                   void* stream) {
+  g_err[0] = 0;
+  if (!weights || !x_mean || !x_dev || !y_mean || !y_dev ||
+      (m > 0 && (!x || !y))) { set_error("an argument is NULL"); return GS_E_INVALID; }
+  if (m < 0) { set_error("m < 0"); return GS_E_INVALID; }
+  return finish(launch_mlp_predict(weights, x, m, MlpNorm{x_mean, x_dev, y_mean, y_dev},
+                                   y, (hipStream_t)stream), "mlp_predict");
+}
+
+int gs_mlp_train_step(float* weights, const float* x, const float* target,
+                      int32_t m, const float* x_mean, const float* x_dev,
+                      const float* y_mean, const float* y_dev, float* scratch,
+                      double* loss_dev, float* dweights, float* adam_m,
+                      float* adam_v, float lr, float beta1, float beta2,
+                      float eps, int32_t step, void* stream) {
+  g_err[0] = 0;
+  if (!weights || !x || !target || !x_mean || !x_dev || !y_mean || !y_dev ||
+      !scratch || !loss_dev || !dweights || !adam_m || !adam_v) { set_error("an argument is NULL"); return GS_E_INVALID; }
+  if (m < 1 || m > 0x7fffffff / 128) { set_error("need 1 <= m < 2^24"); return GS_E_INVALID; }
+  if (step < 1) { set_error("step must be >= 1"); return GS_E_INVALID; }
+  return finish(launch_mlp_train(weights, x, target, m,
+                                 MlpNorm{x_mean, x_dev, y_mean, y_dev}, scratch,
+                                 loss_dev, dweights, adam_m, adam_v, lr, beta1,
+                                 beta2, eps, step, (hipStream_t)stream),
+                "mlp_train_step");
+}
+
 int gs_read_status(gs_workspace* ws, void* stream, int32_t* flags,
                    int64_t* n_keys, int32_t clear) {
   g_err[0] = 0;

@@ -70,8 +70,6 @@ hipError_t launch_knn_features(const gs_params* p, const gs_camera* cam, int W,
                                int n_pts, int centre_only, float* feats,
                                int32_t* knn_idx, float* knn_dist,
                                hipStream_t st);
-hipError_t launch_mlp_fwd(const float* w, const float* x, int M, float* y,
-                          float* cache, hipStream_t st);
 hipError_t launch_mlp_bwd(const float* w, const float* x, const float* cache,
                           const float* dy, int M, float* dw, hipStream_t st);
 hipError_t launch_mlp_mse(const float* y, const float* t, int M, float* dy,
@@ -253,8 +251,19 @@ hipError_t launch_knn_features(const gs_params* p, const gs_camera* cam, int W,
                                int n_pts, int centre_only, float* feats,
                                int32_t* knn_idx, float* knn_dist,
                                hipStream_t st);
+// Feature and output normalisation of the initialisation network: [32] and
+// [7] means and deviations.
+struct MlpNorm {
+  const float *x_mu, *x_sd, *y_mu, *y_sd;
+};
 hipError_t launch_mlp_fwd(const float* w, const float* x, int M, float* y,
                           float* cache, hipStream_t st);
+hipError_t launch_mlp_predict(const float* w, const float* x, int M,
+                              const MlpNorm& nm, float* y, hipStream_t st);
+hipError_t launch_mlp_train(float* w, const float* x, const float* t, int M,
+                            const MlpNorm& nm, float* scratch, double* loss,
+                            float* g, float* m, float* v, float lr, float b1,
+                            float b2, float eps, int step, hipStream_t st);
 hipError_t launch_mlp_bwd(const float* w, const float* x, const float* cache,
                           const float* dy, int M, float* dw, hipStream_t st);
 hipError_t launch_mlp_mse(const float* y, const float* t, int M, float* dy,

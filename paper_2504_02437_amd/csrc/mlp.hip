@@ -75,6 +75,13 @@ __device__ __forceinline__ s4v weight_frag(const float* w, int ldb, int k, int c
                           w[(k + 2) * ldb + c], w[(k + 3) * ldb + c]));
 }
 
+// (v - mean) / deviation per component, correctly rounded like the separate
+// operations it stands for.
+__device__ __forceinline__ float4 normalised(float4 v, float4 mu, float4 sd) {
+  return make_float4((v.x - mu.x) / sd.x, (v.y - mu.y) / sd.y,
+                     (v.z - mu.z) / sd.z, (v.w - mu.w) / sd.w);
+}
+
 // A workgroup of four waves takes 16 rows at a time through all three
 // layers; wave v computes the columns 16 v .. of both hidden layers, so its
 // weights (6 operands, and the 4 of the last layer) stay in registers, read
@@ -82,9 +89,16 @@ __device__ __forceinline__ s4v weight_frag(const float* w, int ldb, int k, int c
 // latency (weights, rows, three dependent layers): 864 rows 4.6 us, 8,192
 // rows 6.7 us; with 64 rows per workgroup, weights staged in LDS and two-byte
 // operand reads 16.4 us (14 workgroups) and 21.2 us.
+// NORM: the features are normalised as they are read, and with `denorm` the
+// outputs are brought back as they are written (a prediction: four launches
+// of 3.2 us each less), or the gradient vector g and the loss are cleared for
+// the rest of a training step.
+template <bool NORM>
 __global__ __launch_bounds__(256) void k_mlp_fwd(const float* w, const float* x,
                                                  int M, float* y, float* cache,
-                                                 bool aligned) {
+                                                 bool aligned, MlpNorm nm,
+                                                 bool denorm, float* g,
+                                                 double* loss) {
   __shared__ __align__(16) unsigned short h1[16 * kLd], h2[16 * kLd];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int m = lane & 15, q = 4 * (lane >> 4);
@@ -101,12 +115,33 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(const float* w, const float* x,
   }
   const float b1 = w[kOffB1 + c], b2 = w[kOffB2 + c];
   const float b3 = m < kOut ? w[kOffB3 + m] : 0.f;
+  float4 mu[2], sd[2];
+  float out_mu = 0.f, out_sd = 1.f;
+  if (NORM) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      mu[i] = load4(nm.x_mu + 16 * i + q, false);
+      sd[i] = load4(nm.x_sd + 16 * i + q, false);
+    }
+    if (denorm && m < kOut) {
+      out_mu = nm.y_mu[m];
+      out_sd = nm.y_sd[m];
+    }
+    if (g)
+      for (int i = blockIdx.x * 256 + threadIdx.x; i < kParams; i += gridDim.x * 256)
+        g[i] = 0.f;
+    if (loss && blockIdx.x == 0 && threadIdx.x == 0) *loss = 0.0;
+  }
   const int blocks = (M + 15) / 16;
   for (int b = blockIdx.x, t = 0; b < blocks; b += gridDim.x, ++t) {
     const int row0 = 16 * b;
     const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
     const float* xr = x + (size_t)min(row0 + m, M - 1) * kIn + q;
     float4 xa = load4(xr, aligned), xb = load4(xr + 16, aligned);
+    if (NORM) {
+      xa = normalised(xa, mu[0], sd[0]);
+      xb = normalised(xb, mu[1], sd[1]);
+    }
     if (row0 + m >= M) xa = xb = zero;
     f4v z = {0.f, 0.f, 0.f, 0.f};
     z = mfma(pack(xa), w1[0], z);
@@ -136,8 +171,11 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(const float* w, const float* x,
     for (int i = 0; i < 4; ++i) z = mfma(lds4(h2 + m * kLd + 16 * i + q), w3[i], z);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      if (m < kOut && row0 + q + i < M)
-        y[(size_t)(row0 + q + i) * kOut + m] = z[i] + b3;
+      if (m < kOut && row0 + q + i < M) {
+        float v = z[i] + b3;
+        if (NORM && denorm) v = __fadd_rn(__fmul_rn(v, out_sd), out_mu);
+        y[(size_t)(row0 + q + i) * kOut + m] = v;
+      }
   }
 }
 
@@ -163,9 +201,10 @@ struct MlpBwdShared {
 };
 constexpr int kBwdThreads = 1024;
 
+template <bool NORM>
 __global__ __launch_bounds__(kBwdThreads) void k_mlp_bwd(
     const float* w, const float* x, const float* cache, const float* dy, int M,
-    float* dw, bool aligned) {
+    float* dw, bool aligned, MlpNorm nm) {
   __shared__ __align__(16) MlpBwdShared S;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int m = lane & 15, q = 4 * (lane >> 4);
@@ -204,8 +243,13 @@ __global__ __launch_bounds__(kBwdThreads) void k_mlp_bwd(
     }
     const int xc = tid & 31, xr = 2 * (tid >> 5);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-      xv[i] = row0 + xr + i < M ? x[(size_t)(row0 + xr + i) * kIn + xc] : 0.f;
+    for (int i = 0; i < 2; ++i) {
+      xv[i] = 0.f;
+      if (row0 + xr + i < M) {
+        xv[i] = x[(size_t)(row0 + xr + i) * kIn + xc];
+        if (NORM) xv[i] = (xv[i] - nm.x_mu[xc]) / nm.x_sd[xc];
+      }
+    }
     __syncthreads();   // the previous rows' products are done
     *(uint32_t*)(S.x + xc * kLd + xr) =
         (uint32_t)to_bf16(xv[0]) | ((uint32_t)to_bf16(xv[1]) << 16);
@@ -299,13 +343,15 @@ __global__ __launch_bounds__(kBwdThreads) void k_mlp_bwd(
   }
 }
 
+template <bool NORM>
 __global__ __launch_bounds__(256) void k_mlp_mse(const float* y, const float* t,
                                                  int n, float scale, float* dy,
-                                                 double* loss) {
+                                                 double* loss, MlpNorm nm) {
   __shared__ double part[4];
   double s = 0.0;
   for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
-    const float d = y[i] - t[i];
+    const int c = i % kOut;
+    const float d = y[i] - (NORM ? (t[i] - nm.y_mu[c]) / nm.y_sd[c] : t[i]);
     dy[i] = scale * d;
     s += (double)d * (double)d;
   }
@@ -340,17 +386,51 @@ constexpr int kBwdBlocks = 256;
 hipError_t launch_mlp_fwd(const float* w, const float* x, int M, float* y,
                           float* cache, hipStream_t st) {
   if (M > 0)
-    hipLaunchKernelGGL(k_mlp_fwd, dim3(min((M + 15) / 16, 1024)), dim3(256), 0,
-                       st, w, x, M, y, cache, ((uintptr_t)x & 15) == 0);
+    hipLaunchKernelGGL(k_mlp_fwd<false>, dim3(min((M + 15) / 16, 1024)),
+                       dim3(256), 0, st, w, x, M, y, cache,
+                       ((uintptr_t)x & 15) == 0, MlpNorm{}, false, nullptr,
+                       nullptr);
   return hipGetLastError();
+}
+
+hipError_t launch_mlp_predict(const float* w, const float* x, int M,
+                              const MlpNorm& nm, float* y, hipStream_t st) {
+  if (M > 0)
+    hipLaunchKernelGGL(k_mlp_fwd<true>, dim3(min((M + 15) / 16, 1024)),
+                       dim3(256), 0, st, w, x, M, y, nullptr,
+                       ((uintptr_t)x & 15) == 0, nm, true, nullptr, nullptr);
+  return hipGetLastError();
+}
+
+// One training step (M > 0).  scratch: [M][128] pre-activations, [M][7]
+// outputs, [M][7] their gradient.  Four launches; features and targets are
+// normalised where they are read (8,192 rows: 66 us with four launches for
+// that and two to clear, bound by issuing them).
+hipError_t launch_mlp_train(float* w, const float* x, const float* t, int M,
+                            const MlpNorm& nm, float* scratch, double* loss,
+                            float* g, float* m, float* v, float lr, float b1,
+                            float b2, float eps, int step, hipStream_t st) {
+  float* cache = scratch;
+  float* y = cache + (size_t)M * 128;
+  float* dy = y + (size_t)M * kOut;
+  hipLaunchKernelGGL(k_mlp_fwd<true>, dim3(min((M + 15) / 16, 1024)), dim3(256),
+                     0, st, w, x, M, y, cache, ((uintptr_t)x & 15) == 0, nm,
+                     false, g, loss);
+  const int n = M * kOut;
+  hipLaunchKernelGGL(k_mlp_mse<true>, dim3(min((n + 255) / 256, 120)),
+                     dim3(256), 0, st, y, t, n, 2.f / (float)n, dy, loss, nm);
+  hipLaunchKernelGGL(k_mlp_bwd<true>, dim3(min((M + 63) / 64, kBwdBlocks)),
+                     dim3(kBwdThreads), 0, st, w, x, cache, dy, M, g,
+                     ((uintptr_t)w & 15) == 0, nm);
+  return launch_mlp_adam(w, g, m, v, lr, b1, b2, eps, step, st);
 }
 
 hipError_t launch_mlp_bwd(const float* w, const float* x, const float* cache,
                           const float* dy, int M, float* dw, hipStream_t st) {
   if (M > 0)
-    hipLaunchKernelGGL(k_mlp_bwd, dim3(min((M + 63) / 64, kBwdBlocks)),
+    hipLaunchKernelGGL(k_mlp_bwd<false>, dim3(min((M + 63) / 64, kBwdBlocks)),
                        dim3(kBwdThreads), 0, st, w, x, cache, dy, M, dw,
-                       ((uintptr_t)w & 15) == 0);
+                       ((uintptr_t)w & 15) == 0, MlpNorm{});
   return hipGetLastError();
 }
 
@@ -360,8 +440,8 @@ hipError_t launch_mlp_mse(const float* y, const float* t, int M, float* dy,
   if (n <= 0) return hipSuccess;
   int blocks = (n + 255) / 256;
   if (blocks > 120) blocks = 120;
-  hipLaunchKernelGGL(k_mlp_mse, dim3(blocks), dim3(256), 0, st, y, t, n,
-                     2.f / (float)n, dy, loss);
+  hipLaunchKernelGGL(k_mlp_mse<false>, dim3(blocks), dim3(256), 0, st, y, t, n,
+                     2.f / (float)n, dy, loss, MlpNorm{});
   return hipGetLastError();
 }
 

@@ -60,14 +60,41 @@ class InitMLP:
         R.mlp_fwd(self.w, x_norm, y, cache)
         return y
 
+    def _plain(self, x, t=None):
+        """Whether the fused calls take these tensors: contiguous float32
+        rows of the network's widths on its device, and the normalisation
+        vectors likewise.  Anything else goes operation by operation."""
+        vec = ((self.x_mu, 32), (self.x_sd, 32), (self.t_mu, 7), (self.t_sd, 7))
+        rows = ((x, 32),) if t is None else ((x, 32), (t, 7))
+        ok = all(v.shape == (n,) for v, n in vec) and \
+            all(r.dim() == 2 and r.shape[1] == n for r, n in rows)
+        return ok and 0 < x.shape[0] < 2 ** 24 and \
+            (t is None or t.shape[0] == x.shape[0]) and \
+            all(v.dtype == torch.float32 and v.device == self.w.device and
+                v.is_cuda and v.is_contiguous() and not v.requires_grad
+                for v, _ in vec + rows)
+
     def predict(self, feats):
         """Initial parameters [M][7] (log-scale 3, opacity logit, RGB 3)."""
+        if self._plain(feats):
+            y = torch.empty(feats.shape[0], 7, device=feats.device)
+            R.mlp_predict(self.w, feats, self.x_mu, self.x_sd, self.t_mu,
+                          self.t_sd, y)
+            return y
         y = self.forward_raw(self._xin(feats))
         return (y * self.t_sd + self.t_mu).contiguous()
 
     def train_step(self, x, t, lr=1e-3, b1=0.9, b2=0.999, eps=1e-8):
         """One Adam step on the MSE of normalised targets; returns the loss
         (device tensor)."""
+        if self._plain(x, t):
+            self.step += 1
+            scratch = torch.empty(x.shape[0] * 142, device=x.device)
+            loss = torch.empty(1, dtype=torch.float64, device=x.device)
+            R.mlp_train_step(self.w, x, t, self.x_mu, self.x_sd, self.t_mu,
+                             self.t_sd, scratch, loss, self.g, self.m, self.v,
+                             lr, b1, b2, eps, self.step)
+            return loss
         xn = self._xin(x)
         tn = ((t - self.t_mu) / self.t_sd).contiguous()
         M = xn.shape[0]

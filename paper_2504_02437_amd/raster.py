@@ -575,6 +575,22 @@ def mlp_adam(weights, dweights, m, v, lr, beta1, beta2, eps, step,
            _stream(stream))
 
 
+def mlp_predict(weights, x, x_mu, x_sd, y_mu, y_sd, y, stream=None):
+    L.call("gs_mlp_predict", _ptr(weights), _ptr(x), int(x.shape[0]),
+           _ptr(x_mu), _ptr(x_sd), _ptr(y_mu), _ptr(y_sd), _ptr(y),
+           _stream(stream))
+
+
+def mlp_train_step(weights, x, target, x_mu, x_sd, y_mu, y_sd, scratch,
+                   loss_dev, dweights, m, v, lr, beta1, beta2, eps, step,
+                   stream=None):
+    L.call("gs_mlp_train_step", _ptr(weights), _ptr(x), _ptr(target),
+           int(x.shape[0]), _ptr(x_mu), _ptr(x_sd), _ptr(y_mu), _ptr(y_sd),
+           _ptr(scratch), _ptr(loss_dev), _ptr(dweights), _ptr(m), _ptr(v),
+           float(lr), float(beta1), float(beta2), float(eps), int(step),
+           _stream(stream))
+
+
 def read_status(ws, stream=None, clear=False):
     flags = C.c_int32()
     nk = C.c_int64()
