@@ -532,28 +532,45 @@ void k_project_bwd(ProjBwdArgs a) {
           4.0 * z * (dR[0] + dR[4]);
   const double dot = dq[0] * w + dq[1] * x + dq[2] * y + dq[3] * z;
   const bool any = S.ok;
+  // All loads of the accumulation, then all stores: a load behind a store
+  // waits for its own latency, the compiler not knowing the rows apart (10k
+  // Gaussians 9.1 us, now 7.1; 10 views of 300k 58 us, now 52.5).
+  float om[3], ol[3], oq[4], orgb[3] = {0.f, 0.f, 0.f};
   for (int j = 0; j < 3; ++j) {
-    a.d_mean[j * cap + g] += (float)dmu[j];
-    if (any) a.d_lsc[j * cap + g] += (float)(ds[j] * S.s[j]);
+    om[j] = a.d_mean[j * cap + g];
+    ol[j] = a.d_lsc[j * cap + g];
+    if (WINDOW) orgb[j] = a.d_rgb[(size_t)j * cap + g];
+  }
+  for (int j = 0; j < 4; ++j) oq[j] = a.d_quat[j * cap + g];
+  const float oo = a.d_opl[g], logit = a.opl[g];
+  double gop = 0.0;
+  double2 sum0, sum1;
+  if (WINDOW) {
+    const double2* p = a.gsum + 2 * (size_t)g;
+    sum0 = p[0];
+    sum1 = p[1];
+  } else {
+    gop = a.gop[g];
+  }
+  for (int j = 0; j < 3; ++j) {
+    a.d_mean[j * cap + g] = om[j] + (float)dmu[j];
+    if (any) a.d_lsc[j * cap + g] = ol[j] + (float)(ds[j] * S.s[j]);
   }
   if (any)
     for (int j = 0; j < 4; ++j)
-      a.d_quat[j * cap + g] += (float)((dq[j] - S.qn[j] * dot) / S.qnorm);
-  double gop;
+      a.d_quat[j * cap + g] = oq[j] + (float)((dq[j] - S.qn[j] * dot) / S.qnorm);
   if (WINDOW) {
     double2* p = a.gsum + 2 * (size_t)g;
-    const double2 q = p[0], r = p[1];
     p[0] = p[1] = make_double2(0.0, 0.0);
-    a.d_rgb[g] += (float)q.x;
-    a.d_rgb[cap + g] += (float)q.y;
-    a.d_rgb[2 * (size_t)cap + g] += (float)r.x;
-    gop = r.y;
+    a.d_rgb[g] = orgb[0] + (float)sum0.x;
+    a.d_rgb[cap + g] = orgb[1] + (float)sum0.y;
+    a.d_rgb[2 * (size_t)cap + g] = orgb[2] + (float)sum1.x;
+    gop = sum1.y;
   } else {
-    gop = a.gop[g];
     a.gop[g] = 0.f;
   }
-  const double o = 1.0 / (1.0 + exp(-(double)a.opl[g]));
-  a.d_opl[g] += (float)(gop * o * (1.0 - o));
+  const double o = 1.0 / (1.0 + exp(-(double)logit));
+  a.d_opl[g] = oo + (float)(gop * o * (1.0 - o));
 }
 
 }  // namespace
