@@ -24,7 +24,8 @@ namespace gs {
 struct __align__(16) Entry {
   float4 a;   // px, py, A2, B2
   float4 b;   // C2, log2(opacity), r, g
-  float4 c;   // b, A, B, C (unscaled conic, for the backward)
+  float4 c;   // b, A, B, C (unscaled conic, for the backward); r, g, b are
+              // consecutive words
   int4 box;   // u_lo, u_hi, v_lo, v_hi
 };
 
@@ -199,8 +200,10 @@ __device__ inline void publish_masks(WaveMasks<BATCH, NT>& m, int i0,
 // per lane and one entry at a time a wave spends 470 cycles on each entry of
 // its list, a chain of some sixty instructions, and while the tiles leave
 // SIMDs idle that chain is the time; here four entries share the step.
-// Forward / backward us at 80 tiles (160x120) 18.7 / 29.7 -> 9.4 / 15.2, at
-// 300 tiles (320x240) 28 / 47 -> 19 / 33 and 5 for k_spread.  Bound then by
+// Forward / backward us at 80 tiles (160x120) 18.7 / 29.7 -> 10.3 / 14.1, at
+// 300 tiles (320x240) 28 / 47 -> 21 / 33, and 5 for k_spread (a colour summed
+// per row and joined at the end 9.4 and 19, but other last bits, on which the
+// sign of an L1 term can turn).  Bound then by
 // staging (9 k of 22 k cycles: four loads one after the other, the ellipse
 // tests) and, at 300 tiles, by instruction issue.
 struct BlockLayout {
@@ -351,12 +354,12 @@ inline RasterShape raster_shape(const gs_workspace* ws, const gs_settings* s) {
 
 // Whether the pass takes the split shape (BlockLayout): open threads, a tile
 // below 32 and few blocks.  Forward / backward us, one workgroup per tile
-// against blocks, gradients by the cheaper of planar rows and accumulators:
-//   tile 16: 80 tiles (160x120) 42 / 32, 37 / 25; 180 tiles 48 / 38, 40 / 33;
-//   300 tiles (320x240) 53 / 48, 47 / 47; 475 tiles 61 / 64, 62 / 75; 1,200
+// against blocks:
+//   tile 16: 80 tiles (160x120) 42 / 32, 38 / 27; 180 tiles 48 / 38, 42 / 33;
+//   300 tiles (320x240) 53 / 48, 50 / 47; 475 tiles 61 / 64, 65 / 75; 1,200
 //   tiles (640x480) 94 / 107, 111 / 161;
-//   tile 8: 300 tiles (160x120) 42 / 31, 38 / 25; 1,200 tiles (320x240) 58 /
-//   60, 51 / 46; 1,900 tiles 76 / 89, 73 / 74; 4,800 tiles 84 / 101, 94 / 109.
+//   tile 8: 300 tiles (160x120) 42 / 31, 39 / 26; 1,200 tiles (320x240) 58 /
+//   60, 54 / 46; 1,900 tiles 76 / 89, 77 / 74; 4,800 tiles 84 / 101, 94 / 109.
 // The backward of tile 8 gains for longer because a tile's own workgroup is a
 // single wave there.
 inline bool split_shape(const gs_workspace* ws, const gs_settings* s,
@@ -365,7 +368,7 @@ inline bool split_shape(const gs_workspace* ws, const gs_settings* s,
   if (s->block_threads != 0 || tile >= 32) return false;
   const long long blocks = (long long)ws->geo.n_views * ws->tiles_x *
                            ws->tiles_y * tile_parts(tile);
-  return blocks < (!backward ? 1900 : tile == 16 ? 1300 : 3000);
+  return blocks < (backward && tile == 8 ? 3000 : 1300);
 }
 
 // Calls launcher.template go<TILE, BATCH, NT>() for a supported shape.

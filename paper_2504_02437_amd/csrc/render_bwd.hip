@@ -776,10 +776,12 @@ __global__ __launch_bounds__(1024) void k_l1_reduce(L1ReduceJob j) {
 // entry points publish planar rows, so there a pass over the accumulators
 // follows (9 us at 300k Gaussians and one view), which pays at tiles below
 // 32 (1200x680, tile 16: 0.28 -> 0.164 ms with the pass; tile 32: 0.123 ms
-// either way) from this many workgroups on.  Whole backward us, planar rows
+// either way) from this many tiles on.  Whole backward us, planar rows
 // against accumulators: 300 tiles of 16 48 / 52, 475 78 / 64, 690 106 / 82,
-// 1,200 123 / 107; 690 tiles of 8 49 / 46; in blocks, 320 25 / 27, 720 39 /
-// 33, 1,200 67 / 47.  The accumulators are FP64: a Gaussian next to the camera
+// 1,200 123 / 107; 690 tiles of 8 49 / 46.  In blocks it pays from about 450
+// of them (320 25 / 27, 720 39 / 33, 1,200 67 / 47), but the accumulators are
+// taken for all: four times as many FP32 adds per tile into a planar row
+// would double the rounding of the case below.  The accumulators are FP64: a Gaussian next to the camera
 // sums thousands of tiles' parts that mostly cancel, and FP32 adds in
 // whatever order they arrive left its gradient 1.4e-6 to 4.6e-6 off from run
 // to run (now 4.0e-7 on the same input, every run).
@@ -835,7 +837,7 @@ hipError_t launch_render_bwd(gs_workspace* ws, const gs_settings* s,
   const bool split = split_shape(ws, s, true);
   a.tile_blocks = split ? tiles * tile_parts(ws->geo.tile) : tiles;
   const bool spread =
-      !window && ws->geo.tile < 32 && a.tile_blocks >= kSpreadBlocks;
+      !window && ws->geo.tile < 32 && (split || tiles >= kSpreadBlocks);
   const bool acc = window || spread;
   a.gview = acc ? ws->gview : nullptr; a.gsum = acc ? ws->gsum : nullptr;
   a.planar = planar ? *planar : PlanarJob{};

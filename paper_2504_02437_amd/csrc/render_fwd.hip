@@ -306,10 +306,10 @@ __global__ __launch_bounds__(NT) void k_render_fwd(FwdArgs a) {
 // holds pixel p and takes the entries 4 i + r of the wave's list.  A step
 // evaluates alpha of its own entry, hands the four alphas of the pixel to all
 // rows (an entry that does not admit the pixel as 0, which leaves T as it
-// is), and every row runs the pixel's transmittance through the four in
-// order, with the same operations as k_render_fwd, so that T, the decisions
-// and n_last are the same to the bit; the colour is summed per row and joined
-// at the end.
+// is), and every row runs the pixel through the four in order: transmittance,
+// n_last and, in row c < 3, the colour channel c.  The operations and their
+// order are k_render_fwd's, so that the images are the same to the bit (the
+// sign of an L1 term turns on the last bit of a colour).
 template <int TILE>
 __global__ __launch_bounds__(BlockLayout::kThreads)
 void k_render_fwd_split(FwdArgs a) {
@@ -339,7 +339,8 @@ void k_render_fwd_split(FwdArgs a) {
   px.vf = pinned((float)px.v);
   const bool image = px.u < r.W && px.v < r.H;
   const float amin = r.alpha_min, tmin = r.T_min;
-  float T = image ? 1.f : -1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
+  float T = image ? 1.f : -1.f, Cc = 0.f;   // Cc: the row's channel
+  const int channel = min(row, 2);
   int last = 0;
   const Record* rv = r.rec + (size_t)k * r.cap;
   const int2* rbv = r.rbox + (size_t)k * r.cap;
@@ -365,62 +366,59 @@ void k_render_fwd_split(FwdArgs a) {
     const uint16_t* list = lists.list[wave];
     auto at = [&](int i) { return (int)list[min(4 * i + row, n - 1)]; };
     const int steps = (n + 3) >> 2;
-    int j = at(0), jn = at(1);
+    int jn = at(1);
     BlockWords w;
-    w.load(ent[j]);
+    w.load(ent[at(0)]);
+    // The step's four entries and their colour of the row's channel.
+    struct Four {
+      int j[4];
+      float c[4];
+    };
+    auto four = [&](int i) {
+      Four f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        f.j[q] = list[min(4 * i + q, n - 1)];
+        f.c[q] = (&ent[f.j[q]].b.z)[channel];
+      }
+      return f;
+    };
+    Four f = four(0);
 #pragma unroll 2
     for (int i = 0; i < steps; ++i) {
       if (__builtin_amdgcn_ballot_w64(T > 0.f) == 0) break;
       BlockWords wn;
       wn.load(ent[jn]);
       const int jnn = at(i + 2);
+      const Four fn = four(i + 1);
       float dx, dy;
       int out;
       const float oG = block_alpha(w, px, dx, dy, out);
       const float al0 = fminf(amax, oG);
       // Past the list's end the last entry stands again: not admitted.
       out |= n - 1 - 4 * i - row;
-      const float al = out >= 0 ? (al0 >= amin ? al0 : 0.f) : 0.f;
-      const Rows x = all_rows(al);
-      float Town = T;
+      const Rows x = all_rows(out >= 0 ? (al0 >= amin ? al0 : 0.f) : 0.f);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        if (q) Town = row == q ? T : Town;
         const float Tn = fmaf(-x.v[q], T, T);
-        T = Tn >= tmin ? Tn : -fabsf(T);
+        const bool con = Tn >= tmin;
+        const float wt = con ? x.v[q] * T : 0.f;
+        Cc = fmaf(f.c[q], wt, Cc);
+        last = con && x.v[q] > 0.f ? base + f.j[q] : last;
+        T = con ? Tn : -fabsf(T);
       }
-      const float Tn = fmaf(-al, Town, Town);
-      const bool con = Tn >= tmin;
-      const float wt = con ? al * Town : 0.f;
-      C0 = fmaf(w.b.z, wt, C0);
-      C1 = fmaf(w.b.w, wt, C1);
-      C2 = fmaf(w.cb, wt, C2);
-      const int idx = al > 0.f ? base + j : 0;
-      last = con ? max(last, idx) : last;
       w = wn;
-      j = jn;
       jn = jnn;
+      f = fn;
     }
   }
-  // Sums over the rows, in every row.
-  auto joined = [](float x) {
-    const Rows v = all_rows(x);
-    return (v.v[0] + v.v[1]) + (v.v[2] + v.v[3]);
-  };
-  C0 = joined(C0);
-  C1 = joined(C1);
-  C2 = joined(C2);
-  const Rows l = all_rows(__int_as_float(last));
-#pragma unroll
-  for (int q = 0; q < 4; ++q) last = max(last, __float_as_int(l.v[q]));
   if (!image) return;
   const float Tf = fabsf(T);
   const size_t HW = (size_t)r.H * r.W;
   const size_t pix = (size_t)px.v * r.W + px.u;
   if (row < 3) {   // a row per channel
     const float bg = row == 0 ? r.bg0 : row == 1 ? r.bg1 : r.bg2;
-    const float c = row == 0 ? C0 : row == 1 ? C1 : C2;
-    a.rgb[((size_t)k * 3 + row) * HW + pix] = fmaf(Tf, bg, c);
+    a.rgb[((size_t)k * 3 + row) * HW + pix] = fmaf(Tf, bg, Cc);
   } else {
     a.T[(size_t)k * HW + pix] = Tf;
     a.nlast[(size_t)k * HW + pix] = last;

@@ -1,5 +1,5 @@
 """The compositing backward's per-Gaussian FP64 accumulators: the entry points
-that pass through them (tiles below 32, 450 workgroups and more) publish the same planar gradients as the direct adds, and leave the
+that pass through them (tiles below 32, 450 tiles and more) publish the same planar gradients as the direct adds, and leave the
 accumulators clear."""
 import numpy as np
 import pytest
