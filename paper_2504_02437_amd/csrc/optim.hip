@@ -204,11 +204,11 @@ __device__ inline void back_project(const gs_camera& cam, int u, int v,
 constexpr int kInsThreads = 1024;
 
 // One workgroup, so that the kept candidates are appended in their order.
-// What bounds it is latency: the loads a candidate needs whether it is kept
-// or not come first, the ranks by ballot within a wave and over the waves'
+// What bounds it is latency: what a candidate needs whether it is kept or not
+// (loads, back-projection, logarithm) comes first, the ranks by ballot within a wave and over the waves'
 // counts, one barrier per 1,024 candidates (864 candidates, by distance and
 // with the network: 8.9 and 8.3 us with the ranks by a doubling scan of 20
-// barriers and the loads behind it, now 8.3 and 7.0).
+// barriers and the rest behind it, now 7.2 and 6.7).
 __global__ __launch_bounds__(kInsThreads) void k_insert(InsertArgs a) {
   constexpr int kWaves = kInsThreads / 64;
   __shared__ int counts[2][kWaves];
@@ -223,6 +223,7 @@ __global__ __launch_bounds__(kInsThreads) void k_insert(InsertArgs a) {
     bool keep = false;
     int u = 0, v = 0;
     float d = 0.f, val[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    double X[3];
     if (c < total) {
       const int patch = c / per;
       const int pix = a.centre_only ? 4 : c - patch * per;
@@ -236,7 +237,10 @@ __global__ __launch_bounds__(kInsThreads) void k_insert(InsertArgs a) {
         } else {
           for (int i = 0; i < 3; ++i)
             val[4 + i] = a.kf_rgb[((size_t)i * a.H + v) * a.W + u];
+          const float ls = (float)log(1.0 / (double)d / (double)cam.fx);
+          for (int i = 0; i < 3; ++i) val[i] = ls;
         }
+        back_project(cam, u, v, (double)d, X);
         if (a.d2bits) {
           const unsigned long long b = a.d2bits[c];
           keep = b == ~0ull || __longlong_as_double((long long)b) > a.tau2;
@@ -260,14 +264,7 @@ __global__ __launch_bounds__(kInsThreads) void k_insert(InsertArgs a) {
       const int rank = before + __popcll(kept & ((1ull << lane) - 1));
       const int dst = n0 + running + rank;
       if (dst < a.cap) {
-        const double z = 1.0 / (double)d;
-        double X[3];
-        back_project(cam, u, v, (double)d, X);
         for (int i = 0; i < 3; ++i) a.rows[i][dst] = (float)X[i];
-        if (!a.mlp_out) {
-          const float ls = (float)log(z / (double)cam.fx);
-          for (int i = 0; i < 3; ++i) val[i] = ls;
-        }
         for (int i = 0; i < 3; ++i) a.rows[3 + i][dst] = val[i];
         a.rows[10][dst] = val[3];
         for (int i = 0; i < 3; ++i) a.rows[11 + i][dst] = val[4 + i];
