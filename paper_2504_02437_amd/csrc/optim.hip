@@ -205,10 +205,10 @@ constexpr int kInsThreads = 1024;
 
 // One workgroup, so that the kept candidates are appended in their order.
 // What bounds it is latency: what a candidate needs whether it is kept or not
-// (loads, back-projection, logarithm) comes first, the ranks by ballot within a wave and over the waves'
-// counts, one barrier per 1,024 candidates (864 candidates, by distance and
-// with the network: 8.9 and 8.3 us with the ranks by a doubling scan of 20
-// barriers and the rest behind it, now 7.2 and 6.7).
+// (loads, back-projection, logarithm) comes first, the ranks by ballot within
+// a wave and over the waves' counts, one barrier per 1,024 candidates (864
+// candidates, by distance and with the network: 8.9 and 8.3 us with the ranks
+// by a doubling scan of 20 barriers and the rest behind it, now 7.2 and 6.7).
 __global__ __launch_bounds__(kInsThreads) void k_insert(InsertArgs a) {
   constexpr int kWaves = kInsThreads / 64;
   __shared__ int counts[2][kWaves];

@@ -54,6 +54,9 @@ struct BwdArgs {
   // Workgroups past the tiles' (tile_blocks) run the planar regulariser.
   int tile_blocks;
   PlanarJob planar;
+  // Workgroups of k_spread's row past spread_blocks sum the fused L1 losses.
+  int spread_blocks;
+  L1ReduceJob l1;
 };
 
 // Sign of r times scale (sign(0) = 0): the L1 term's gradient.
@@ -724,8 +727,14 @@ void k_render_bwd_split(BwdArgs a) {
 }
 
 // The per-Gaussian accumulators added to the planar gradients and cleared:
-// grid (Gaussians / 256, views).
+// grid (Gaussians / 256, views); one more column where the fused L1 term's
+// losses are to be summed, which saves a launch of 4 us.
 __global__ __launch_bounds__(256) void k_spread(BwdArgs a) {
+  __shared__ double part[4];
+  if ((int)blockIdx.x >= a.spread_blocks) {
+    if (blockIdx.y == 0) l1_reduce_part(a.l1, part);
+    return;
+  }
   const int g = blockIdx.x * 256 + threadIdx.x, k = blockIdx.y;
   const size_t cap = a.r.cap;
   if (g >= a.r.cap) return;
@@ -841,6 +850,8 @@ hipError_t launch_render_bwd(gs_workspace* ws, const gs_settings* s,
   const bool acc = window || spread;
   a.gview = acc ? ws->gview : nullptr; a.gsum = acc ? ws->gsum : nullptr;
   a.planar = planar ? *planar : PlanarJob{};
+  a.spread_blocks = 0;
+  a.l1 = L1ReduceJob{};
   if (tiles <= 0) {
     if (planar) {
       const hipError_t e = launch_planar_job(*planar, st);
@@ -859,8 +870,12 @@ hipError_t launch_render_bwd(gs_workspace* ws, const gs_settings* s,
     if (spread && ws->geo.capacity > 0) {
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
-      hipLaunchKernelGGL(k_spread, dim3((ws->geo.capacity + 255) / 256,
-                                        ws->geo.n_views), dim3(256), 0, st, a);
+      const bool sum = l1 && !l1->defer_reduce;
+      a.spread_blocks = (ws->geo.capacity + 255) / 256;
+      if (sum) a.l1 = l1_reduce_job(ws, s, l1->loss, l1->sqerr);
+      hipLaunchKernelGGL(k_spread, dim3(a.spread_blocks + sum, ws->geo.n_views),
+                         dim3(256), 0, st, a);
+      if (sum) return hipGetLastError();
     }
   }
   if (l1 && !l1->defer_reduce) {

@@ -67,10 +67,12 @@ def test_gradients_match_the_oracle(W, H, n, views, tile, bg):
 
 
 @pytest.mark.parametrize("W,H,views,tile", [(33, 29, 2, 16), (320, 257, 1, 16),
-                                            (320, 256, 1, 16), (45, 70, 1, 8)])
+                                            (320, 256, 1, 16), (45, 70, 1, 8),
+                                            (640, 400, 1, 16), (330, 300, 3, 16)])
 def test_fused_l1_matches_the_separate_loss(W, H, views, tile):
-    """Loss and squared errors (a slot per block), which the fused call sums
-    in a fixed order: the same twice."""
+    """Loss and squared errors (a slot per block or tile), which the fused call
+    sums in a fixed order, by a launch of its own or beside the accumulators'
+    pass: the same twice."""
     w = _scene(W, H, 400, views)
     params, rast = gpu_forward(w, tile, bg=BG)
     rng = np.random.default_rng(9)
