@@ -121,7 +121,7 @@ typedef struct gs_camera {
  *   block_threads  threads per tile workgroup (0 = default); each thread
  *               owns a vertical strip of tile*tile/block_threads pixels:
  *               tile 8: 64; tile 16: 64, 128 or 256 (default by the number of
- *               tiles);
+ *               tiles; few tiles are taken in 8x8 blocks);
  *               tile 32: 128 or 256 (default 256)
  *   bg          background colour added with weight T_final
  *   alpha_min   entries with alpha below this are skipped (1/255)
