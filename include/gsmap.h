@@ -355,14 +355,13 @@ GS_API int gs_loss_l1(const float* rgb, const float* target, int32_t n_views,
  * into ssim_dev[n_views] (device double, may be NULL).
  *   rgb, target, dL_drgb  device float [n_views][3][height][width]
  *   scratch               device float [3][n_views][3][height][width],
- *                         caller-owned, overwritten where dL_drgb shares
- *                         memory with an image, otherwise unused */
+ *                         caller-owned, may be overwritten */
 GS_API int gs_loss_ssim(const float* rgb, const float* target, int32_t n_views,
                         int32_t height, int32_t width, float lambda,
                         float* dL_drgb, double* loss_dev, double* ssim_dev,
                         float* scratch, void* stream);
 
-/* The whole colour loss of Eq. 10 in the one pass of gs_loss_ssim:
+/* The whole colour loss of Eq. 10 as gs_loss_ssim takes its term:
  * lambda_l1 * (L1 term of gs_loss_l1) + lambda_ssim * (SSIM term of
  * gs_loss_ssim), i.e. lambda_color (1 - lambda_photo) and lambda_color
  * lambda_photo.  WRITES dL_drgb (the sum of both gradients), ADDS both terms

@@ -43,6 +43,7 @@ UNITS = [
     ("render_bwd.hip", NO_CONTRACT + NO_ATOMIC_OPT),
     ("optim.hip", []),
     ("ssim.hip", []),
+    ("ssim_tiles.hip", []),
     ("densify.hip", []),
     ("mlp.hip", NO_CONTRACT),
     ("near.hip", NO_CONTRACT),

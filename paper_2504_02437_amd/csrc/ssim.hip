@@ -33,7 +33,8 @@
 // more per step, was 3 % slower.  In place of a statistics and a gradient
 // kernel with the derivative maps in memory between them: ten 680 x 1200 views
 // 282 us (was 405; 9.8 MB per plane in and out), one 44 (92), ten 480 x 640
-// 107 (161), one 251 x 377 17.3 (21.2), one 50 x 85 11.9 (12.5).
+// 107 (161), one 251 x 377 17.3 (21.2).  Small inputs keep those two kernels
+// (ssim_tiles.hip, use_tiles).
 
 #include <float.h>
 #include <math.h>
@@ -469,9 +470,9 @@ struct Split {
 // SIMD holds two waves (registers) and a step of two takes 1.3 times as long
 // as a step of one (a 680 x 1200 view by 256 threads: 252 workgroups of 52 rows
 // take 49 us, 396 of 32 rows 44 us).
-// Workgroups add their sums to the same addresses, 10 ns each (a 251 x 377
-// view: 567 workgroups of 64 threads with eight steps' time, 22.4 us; 432 with
-// nine, 22.4 us).
+// Workgroups add their sums to the same addresses, 10 ns each where they end
+// together (a 251 x 377 view: 567 workgroups of 64 threads with eight steps'
+// time, 22.4 us; 432 with nine, 22.4 us), less where there are many.
 Split split_planes(int planes, int H, int W) {
   const int groups = (H + kRows - 1) / kRows;
   Split best{};
@@ -485,7 +486,7 @@ Split split_planes(int planes, int H, int W) {
       const int g = (int)((groups + parts - 1) / parts);
       const long long n = columns * ((groups + g - 1) / g);
       const long long waves = (n + filled - 1) / filled;
-      const double cost = (waves / 2 * 1.3 + waves % 2) * (g + kLag - 1) + 0.0075 * n;
+      const double cost = (waves / 2 * 1.3 + waves % 2) * (g + kLag - 1) + 0.002 * n;
       if (!best.nt || cost < least) {
         best = {nt, strips, kRows * g};
         least = cost;
@@ -510,11 +511,26 @@ hipError_t launch_loss_ssim(const float* rgb, const float* target, int V,
                             nullptr, ssim, scratch, st);
 }
 
+// Whether the two kernels over 64 x 16 tiles are the faster form: few tiles,
+// where the seven dependent steps of a strip, 1.6 us each, and the adds of the
+// strips' sums to one address are the time; narrow images for longer, since
+// each strip computes 20 columns more than it writes.  Tiles / strips us: ten
+// 64 x 35 (90 tiles) 12.5 / 15.9, five 128 x 70 (150) 13.7 / 15.8, one 256 x
+// 204 (156) 13.9 / 15.9, three 256 x 204 (468) 21.3 / 22.8; ten 100 x 80 (300)
+// 18.1 / 20.6; one 377 x 251 (288) 21.2 / 17.0, eight 256 x 204 (1,248) 38 / 33.
+bool use_tiles(int V, int H, int W) {
+  const long long tiles = 3LL * V * ((W + 63) / 64) * ((H + 15) / 16);
+  return tiles <= 256 || (W <= 256 && tiles <= 600);
+}
+
 hipError_t launch_loss_colour(const float* rgb, const float* target, int V,
                               int H, int W, float lam_l1, float lam,
                               int fuse_l1, float* dL, double* loss,
                               double* sqerr, double* ssim, float* scratch,
                               hipStream_t st) {
+  if (use_tiles(V, H, W))
+    return launch_ssim_tiles(rgb, target, V, H, W, lam_l1, lam, fuse_l1, dL,
+                             loss, sqerr, ssim, scratch, st);
   SsimArgs a;
   {
     double g[2 * kR + 1], sum = 0.0;

@@ -17,9 +17,19 @@ from test_gpu_ssim import _check, _colour, _pair
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(1, 3, 11, 44), (1, 3, 12, 45), (1, 3, 13, 88), (1, 3, 5, 108),
-          (1, 3, 16, 109), (2, 3, 31, 216), (1, 3, 33, 217), (1, 3, 9, 236),
-          (1, 3, 50, 237), (4, 3, 150, 473), (1, 3, 330, 44)]
+
+def _views(H, W):
+    """Views enough for the strips: small inputs are taken in tiles."""
+    tiles = 3 * ((W + 63) // 64) * ((H + 15) // 16)
+    return (601 if W <= 256 else 257) // tiles + 1
+
+
+SHAPES = [(_views(H, W), 3, H, W) for H, W in (
+    (11, 44), (12, 45), (13, 88), (5, 108), (16, 109), (31, 216), (33, 217),
+    (9, 236), (50, 237), (150, 473), (330, 44))]
+# Both sides of the lines between tiles and strips.
+SHAPES += [(1, 3, 250, 344), (1, 3, 257, 344), (5, 3, 160, 256),
+           (5, 3, 161, 256)]
 
 
 @pytest.mark.parametrize("shape", SHAPES)
@@ -45,7 +55,7 @@ def test_strip_edges_fused_equals_l1_then_ssim(shape):
 def test_misaligned_images(which):
     """One of the three images four bytes off a 16-byte line: the same
     gradient as aligned (the same sums, written one by one)."""
-    shape = (1, 3, 21, 240)
+    shape = (_views(21, 240), 3, 21, 240)
     x, y = _pair(13, shape)
     n = x.size
     buf = [torch.zeros(n + 4, device="cuda") for _ in range(3)]
@@ -66,7 +76,7 @@ def test_misaligned_images(which):
 def test_a_value_that_is_not_finite_stays_in_its_windows(at, value):
     """A gradient depends on the pixels at most ten rows and columns away:
     NaN there, and bit for bit as without the value further off."""
-    x, y = _pair(14, (1, 3, 61, 250))
+    x, y = _pair(14, (_views(61, 250), 3, 61, 250))
     good = _colour(x, y, 0.8, 0.2, True)[3][0, 1]
     x[0, 1, at[0], at[1]] = value
     print("case colour not finite", at, value, flush=True)
@@ -77,9 +87,10 @@ def test_a_value_that_is_not_finite_stays_in_its_windows(at, value):
     assert np.isnan(g[0, 1][near]).all()
     np.testing.assert_array_equal(g[0, 1][~near], good[~near])
     assert np.isfinite(g[0, 0]).all() and np.isfinite(g[0, 2]).all()
+    assert np.isfinite(g[1:]).all()
 
 
-@pytest.mark.parametrize("shape", [(2, 3, 30, 300), (1, 3, 9, 45)])
+@pytest.mark.parametrize("shape", [(_views(30, 300), 3, 30, 300), (1, 3, 9, 45)])
 @pytest.mark.parametrize("fused", [False, True])
 def test_gradient_written_over_the_rendering(shape, fused):
     """dL in the memory of the rendered images: as with memory of its own."""
