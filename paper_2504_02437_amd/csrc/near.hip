@@ -335,7 +335,7 @@ __host__ __device__ inline int knn_list(int per) {
   return knn_words(per) - knn_slices(per) - 1;   // behind the count
 }
 
-// The middle of a patch (every lane) and its rho, by one wave.
+// The middle of a patch and its rho (both in every lane), by one wave.
 __device__ inline double patch_middle(const NearArgs& a, int patch,
                                       float* mid) {
   const int lane = threadIdx.x & 63, mi = a.per == 1 ? 0 : 4;
@@ -346,8 +346,10 @@ __device__ inline double patch_middle(const NearArgs& a, int patch,
     mid[i] = __uint_as_float(
         __builtin_amdgcn_readlane(__float_as_uint((float)X[i]), mi));
   double rho = dist2(X, mid[0], mid[1], mid[2]);
-  for (int off = 8; off > 0; off >>= 1) rho = fmax(rho, __shfl_xor(rho, off, 64));
-  return sqrt(rho);   // lanes past the candidates repeat the last one
+  // Lanes past the candidates repeat the last one, so the maximum is taken
+  // over the whole wave.
+  for (int off = 32; off > 0; off >>= 1) rho = fmax(rho, __shfl_xor(rho, off, 64));
+  return sqrt(rho);
 }
 
 // The eighth smallest of the lanes' values >= 0 (as bit patterns), +inf when

@@ -135,3 +135,23 @@ def test_many_patches():
     means = synth.room_gaussians(rng, 30000).mean
     _check(means, cam, _pts(rng, cam, 700), False,
            sample=[0, 15, 16, 333, 699])
+
+
+@pytest.mark.parametrize("corner", [2, 6])
+def test_sheared_camera_beyond_the_list(corner):
+    """A rotation that is not orthonormal: the corners 2 and 6 of a patch are
+    six times as far from its middle as 0 and 8, and the means around one of
+    them, more than a list holds, are its neighbours."""
+    rng = np.random.default_rng(9)
+    print("case near sheared", corner, flush=True)
+    shear = np.array([[1, 0, 0], [-0.9, 0.3, 0], [0, 0, 1]], np.float32)
+    cam = synth.Camera(shear, np.zeros(3, np.float32), 20.0, 20.0, 20.0, 15.0,
+                       40, 30)
+    pts = np.array([[20, 15, 0.5]], np.float32)
+    P = OM.features(cam, np.zeros((3, 30, 40), np.float32), pts,
+                    np.zeros((3, 1)), np.zeros((3, 1)), False)[1]
+    far = [np.linalg.norm(P[i] - P[4]) for i in (0, 2, 6, 8)]
+    assert min(far[1:3]) > 5 * max(far[0], far[3])
+    means = np.repeat(P[[4, corner]], 400, axis=0).T
+    means = means + rng.normal(0, 1e-3, size=means.shape)
+    _check(means.astype(np.float32), cam, pts, False)
