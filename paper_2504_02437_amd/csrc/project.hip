@@ -316,7 +316,9 @@ __device__ __forceinline__ void project_one(const ProjArgs& a, const CamD& cam,
 // dilated covariance has a + c <= |J|_F^2 |W W^T| sum s_j^2 + 0.6, its larger
 // eigenvalue is at most a + c + 0.32, and tz^2 |J|_F^2 <= fx^2 (1 + limx^2) +
 // fy^2 (1 + limy^2); `reach` is that times |W W^T|.  The edges are compared
-// times tz.  FP32 with slack; what is not a number is not culled here.
+// times tz, which holds for tz > 0 only: what a negative near plane lets
+// through behind the camera is not culled here, nor is what is not a number.
+// FP32 with slack.
 __device__ __forceinline__ bool out_of_view(const ProjArgs& a, const CamD& cam,
                                             float reach, int g) {
   const size_t cap = a.cap;
@@ -325,6 +327,7 @@ __device__ __forceinline__ bool out_of_view(const ProjArgs& a, const CamD& cam,
   const double* W = cam.W;
   const double tz = ((W[6] * mx + W[7] * my) + W[8] * mz) + cam.t[2];
   if (tz <= cam.near_z) return true;
+  if (!(tz > 0.0)) return false;
   const float tx = (float)(((W[0] * mx + W[1] * my) + W[2] * mz) + cam.t[0]);
   const float ty = (float)(((W[3] * mx + W[4] * my) + W[5] * mz) + cam.t[1]);
   const float z = (float)tz;

@@ -56,3 +56,23 @@ def test_same_pairs_as_one_by_one(n, scale):
                        b.ws.records()[:, :n][on].view(torch.int32))
     assert torch.equal(a.ws.render_box()[:, :n][on], b.ws.render_box()[:, :n][on])
     assert torch.equal(a.T, b.T) and torch.equal(a.nlast, b.nlast)
+
+
+@pytest.mark.parametrize("near", [-30.0, 0.0, float("nan")])
+def test_near_planes_behind_the_camera(near):
+    """A near plane that lets Gaussians behind the camera through (or, not a
+    number, nothing): the same pairs in either form."""
+    n = 3000
+    w = _scene(17, n, -3.0)
+    for c in w.cameras:
+        c.near = near
+    print("case project shared near", near, flush=True)
+    tiles = []
+    for cap in (n, 1 << 19):
+        params = R.ParamBuffer.from_gaussians(w.gaussians, capacity=cap)
+        _, r = gpu_forward(w, 16, params=params, key_capacity=1 << 18)
+        assert r.status()[0] == 0
+        tiles.append(r.ws.tiles_touched()[:, :n].clone())
+    behind = torch.from_numpy(w.gaussians.mean[2] < 0).cuda()
+    assert bool((tiles[0][0][behind] > 0).any()) == (near < 0)
+    assert torch.equal(tiles[0], tiles[1])
