@@ -237,15 +237,9 @@ __device__ inline void load_owner(const ScatterArgs& a, int n, int k, int g,
   dbits = o.dbits;
 }
 
-// Orders one wave's LDS accesses before and after this point.  The owner
-// table below is private to a wave: its lanes only need to see each other's
-// writes, not the other waves' (a block barrier would make the waves of a
-// workgroup wait for the slowest one).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
+// The owner table is private to a wave: its lanes only need to see each
+// other's writes (wave_sync), not the other waves' (a block barrier would make
+// the waves of a workgroup wait for the slowest one).
 template <typename F>
 __device__ inline void wave_enumerate(WaveOwners& O, int lane, int cnt, int x0,
                                       int y0, int w, uint32_t g, uint32_t dbits,

@@ -8,6 +8,13 @@
 
 namespace gs {
 
+// Orders one wave's LDS accesses before and after this point, where its lanes
+// read what others of them wrote.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // One projected (view, Gaussian) record, 48 bytes = three float4:
 //   q0 = (px, py, A, B), q1 = (C, opacity, r, g),
 //   q2 = (b, depth, u_lo | u_hi << 16, v_lo | v_hi << 16)

@@ -439,12 +439,6 @@ __global__ __launch_bounds__(kThreads) void k_knn_list(NearArgs a) {
   });
 }
 
-// Orders one wave's LDS accesses before and after this point.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 struct Nb {
   double d2;
   int idx;

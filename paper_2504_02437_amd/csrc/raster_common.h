@@ -232,7 +232,8 @@ struct BlockLists {
       if (lane == 0) eval[w][wave] = e;
     }
   }
-  // The wave's list of the entries below jn, in order; returns their number.
+  // The wave's list of the entries below jn, in order, readable by all its
+  // lanes; returns their number.
   __device__ __forceinline__ int gather(int jn, int wave, int lane) {
     int n = 0;
 #pragma unroll
@@ -248,6 +249,7 @@ struct BlockLists {
             (uint16_t)(64 * c + lane);
       n += __builtin_popcountll(e);
     }
+    wave_sync();
     return n;
   }
 };

@@ -281,13 +281,6 @@ __device__ __forceinline__ void sort_in_registers(uint32_t (&x)[E], int L,
   if constexpr (P2 >= 2) merge_steps<E, P2, 2>(x, active, work, lane, buf);
 }
 
-// Orders one wave's LDS accesses before and after this point (the one-wave
-// segments have no other wave to wait for).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 constexpr int kIdxBits = 12;   // position in a segment of at most 4096 keys
 constexpr int kQBits = 32 - kIdxBits;
 
@@ -393,6 +386,7 @@ __device__ void sort_tile(const SortArgs& a, int t, long long s, int L, int nw,
     for (int e = 0; e < E; ++e)
       if (base + e < L) buf[base + e] = x[e];
   }
+  // (A one-wave segment has no other wave to wait for.)
   if (nw > 1) __syncthreads(); else wave_sync();
   if (!active || base >= L) return;
   // The lane's E positions are consecutive, so the runs they fall in cover
