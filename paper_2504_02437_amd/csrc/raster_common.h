@@ -13,6 +13,8 @@
 // which keeps a Gaussian's box test coherent across the wave.
 #pragma once
 
+#include <stddef.h>
+
 #include "admit.h"
 #include "gs_internal.h"
 
@@ -24,10 +26,14 @@ namespace gs {
 struct __align__(16) Entry {
   float4 a;   // px, py, A2, B2
   float4 b;   // C2, log2(opacity), r, g
-  float4 c;   // b, A, B, C (unscaled conic, for the backward); r, g, b are
-              // consecutive words
+  float4 c;   // b, A, B, C (unscaled conic, for the backward)
   int4 box;   // u_lo, u_hi, v_lo, v_hi
+  // Colour channel 0, 1 or 2 (r, g, b are consecutive words of the entry).
+  __device__ __forceinline__ float colour(int channel) const {
+    return ((const float*)this)[offsetof(Entry, b) / 4 + 2 + channel];
+  }
 };
+static_assert(offsetof(Entry, c) == offsetof(Entry, b) + 16, "r, g, b in a row");
 
 template <int TILE, int NT>
 struct PixLayout {

@@ -379,7 +379,7 @@ void k_render_fwd_split(FwdArgs a) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         f.j[q] = list[min(4 * i + q, n - 1)];
-        f.c[q] = (&ent[f.j[q]].b.z)[channel];
+        f.c[q] = ent[f.j[q]].colour(channel);
       }
       return f;
     };
