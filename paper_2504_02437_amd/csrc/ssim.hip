@@ -24,10 +24,15 @@
 // exchange through LDS: 14 reads serve 44 taps.
 // The images are read once (10 rows and columns of overlap around a strip),
 // the gradient is written once; the statistics need only four maps (x, y,
-// x^2 + y^2, x y), since the variances enter as a sum.
+// (x - y)^2, x y):
+//   B1 = A1 + (mu_x - mu_y)^2,  B2 = A2 + var(x - y),
+// so that where the images resemble one another the rounding of A1 and A2 is
+// that of B1 and B2 and leaves the quotients (a sum of x^2 + y^2 in the third
+// map's place is one rounding of twice the size and does not: the gradient of
+// a rendering close to its target was 1.2 times as far off).
 //
 // Bound by the horizontal sums: 308 FMAs per four pixels in a row plus the
-// pointwise terms, about 500 vector instructions, at two waves per SIMD (220
+// pointwise terms, about 500 vector instructions, at two waves per SIMD (240
 // registers for the two sets of 28 open sums; at three the sums spill, 2
 // times slower).  Two sets of LDS buffers instead of three, with a barrier
 // more per step, was 3 % slower.  In place of a statistics and a gradient
@@ -246,6 +251,12 @@ __device__ __forceinline__ void load_rows(const SsimArgs& a, const float* X,
   }
 }
 
+// a b + c d with both products rounded, so that identical images come to 0.
+__device__ __forceinline__ float two_products(float a, float b, float c, float d) {
+#pragma clang fp contract(off)
+  return a * b + c * d;
+}
+
 // Step s (S: modulo 3): four image rows in, four rows of statistics (s - 3),
 // of derivative sums (s - 6) and of the gradient out.  PHASE 0, steps 0-2:
 // no statistics yet; 1, steps 3-5: no gradient yet; 2: all.
@@ -266,11 +277,15 @@ __device__ __forceinline__ void strip_step(const SsimArgs& a, const float* X,
     for (int j = 0; j < kRows; ++j) {
       v[j][0] = st.x[j];
       v[j][1] = st.y[j];
-      v[j][2] = fmaf(st.x[j], st.x[j], st.y[j] * st.y[j]);
+      const float e = st.x[j] - st.y[j];
+      v[j][2] = e * e;
       v[j][3] = st.x[j] * st.y[j];
     }
+    float check = 0.f;
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) check += v[j][2] + v[j][3];
     load_rows(a, X, Y, v0, s + 1, u0 - 2 * kR + tid, st);
-    st.stat.screen((v[0][2] + v[1][2]) + (v[2][2] + v[3][2]), v);
+    st.stat.screen(check, v);
     if constexpr (PHASE >= 1) {
       st.stat.template finish<S>(band, v);
 #pragma unroll
@@ -294,21 +309,24 @@ __device__ __forceinline__ void strip_step(const SsimArgs& a, const float* X,
 #pragma unroll
     for (int o = 0; o < 4; ++o) {
       const float mx = m[o][0], my = m[o][1], mxy = mx * my;
-      const float mm = fmaf(mx, mx, my * my);
+      const float dm = mx - my, d1 = dm * dm;
       const float A1 = fmaf(2.f, mxy, kC1);
       const float A2 = fmaf(2.f, m[o][3] - mxy, kC2);
-      const float B1 = mm + kC1;
-      const float B2 = (m[o][2] - mm) + kC2;
+      const float d2 = fmaf(-dm, dm, m[o][2]);
       // Reciprocals are enough here (the term is compared at 1e-5 / 1e-3).
-      const float iB1 = __builtin_amdgcn_rcpf(B1), iB2 = __builtin_amdgcn_rcpf(B2);
-      const float iB = iB1 * iB2, A1B = A1 * iB, ssim = A2 * A1B;
-      rs += (st.out >> o) & 1 ? ssim : 0.f;
-      // dS/dmu_x = 2 (my (A2 - A1) / (B1 B2) + mx S (1 / B2 - 1 / B1)).
-      const float q = (st.in >> o) & 1 ? row_scale : 0.f, q2 = q + q;
+      const float iB1 = __builtin_amdgcn_rcpf(A1 + d1);
+      const float iB2 = __builtin_amdgcn_rcpf(A2 + d2);
+      // q1 = A1 / B1 and q2 = A2 / B2; f1 and f2 what they lack of 1.
+      const float q1 = A1 * iB1, f1 = d1 * iB1, f2 = d2 * iB2, q2 = 1.f - f2;
+      rs += (st.out >> o) & 1 ? q1 * (A2 * iB2) : 0.f;
+      // dS/dmu_x = 2 (q1 (dm - mx f2) / B2 + q2 (mx f1 - dm) / B1),
+      // dS/dm_xx = -q1 q2 / B2, dS/dm_xy = 2 q1 / B2.
+      const float q = (st.in >> o) & 1 ? row_scale : 0.f, qq = q + q;
+      const float qB2 = q1 * iB2;
       float4 d;
-      d.x = q2 * fmaf(my * iB, A2 - A1, mx * ssim * (iB2 - iB1));
-      d.y = -q * (ssim * iB2);
-      d.z = q2 * A1B;
+      d.x = qq * fmaf(qB2, fmaf(-mx, f2, dm), (iB1 * q2) * fmaf(mx, f1, -dm));
+      d.y = (-q * qB2) * q2;
+      d.z = qq * qB2;
       d.w = 0.f;
       sh.d.v[row][Exchange<NT>::at(c0 + o)] = d;
     }
@@ -376,8 +394,7 @@ __device__ __forceinline__ void strip_step(const SsimArgs& a, const float* X,
       st.ls += fabsf(e);
       st.sqsum += (double)e * (double)e;
     }
-    const float t = fmaf(y[o], m[o][2], fmaf(2.f * x[o], m[o][1], m[o][0]));
-    g[o] = g[o] + t;
+    g[o] = g[o] + (m[o][0] + two_products(2.f * x[o], m[o][1], y[o], m[o][2]));
   }
   if (a.aligned) {
     *(float4*)(G + po) = make_float4(g[0], g[1], g[2], g[3]);
