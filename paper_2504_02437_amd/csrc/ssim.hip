@@ -60,6 +60,7 @@ constexpr int kRows = 4;                // rows per step
 constexpr int kSpan = kTaps + kRows - 1;   // inputs of four outputs (14)
 constexpr int kLag = 6;                 // steps from a row's load to its output
 constexpr float kC1 = 0.01f * 0.01f, kC2 = 0.03f * 0.03f;
+constexpr float kBig = 1e37f;           // its reciprocal is a normal number
 
 struct SsimArgs {
   float w[kR + 1];      // normalised 1D window, taps 0 .. 5 (symmetric)
@@ -92,23 +93,33 @@ struct SsimArgs {
 // It multiplies every input row by every weight, and 0 times infinity or NaN
 // would reach output rows whose window does not hold that input.  Rows that
 // are not finite are therefore added as zeros and the windows that hold them
-// are set to NaN (what their statistics come to in any case).
+// are set to NaN, what their statistics come to in any case.  Of the four
+// maps of the statistics the squares alone may run over, where they still
+// come to an SSIM of 0: these are added as zeros too, and their map's windows
+// set to infinity.
 template <int N>
 struct VerticalSums {
   f4v acc[N][3];
-  unsigned bad;   // bit b: the input row 3 - b (of this step) is not finite
+  static constexpr int kSquares = N == 4 ? 2 : -1;   // the statistics' map
+  unsigned bad;   // bit b: the input row 3 - b (of this step) is not finite,
+                  // bit 16 + b: only its squares are not
   // check: not finite where one of v is not.
   __device__ __forceinline__ void screen(float check, float (&v)[kRows][N]) {
-    bad = (bad << kRows) & 0xffffu;
+    bad = (bad << kRows) & 0xfff0fff0u;
     if (!__any(!(fabsf(check) <= FLT_MAX))) return;
 #pragma unroll
     for (int j = 0; j < kRows; ++j) {
-      bool finite = true;
+      bool finite = true, square = true;
 #pragma unroll
-      for (int m = 0; m < N; ++m) finite = finite && fabsf(v[j][m]) <= FLT_MAX;
-      bad |= finite ? 0u : 1u << (kRows - 1 - j);
+      for (int m = 0; m < N; ++m) {
+        const bool f = fabsf(v[j][m]) <= FLT_MAX;
+        if (m == kSquares) square = f;
+        else finite = finite && f;
+      }
+      bad |= (finite ? square ? 0u : 0x10000u : 1u) << (kRows - 1 - j);
 #pragma unroll
-      for (int m = 0; m < N; ++m) v[j][m] = finite ? v[j][m] : 0.f;
+      for (int m = 0; m < N; ++m)
+        v[j][m] = finite && (m != kSquares || square) ? v[j][m] : 0.f;
     }
   }
   // Output row i of the finished group takes the input rows i - 12 .. i - 2.
@@ -116,8 +127,13 @@ struct VerticalSums {
   __device__ __forceinline__ void mark() {
     if (!__any(bad)) return;
 #pragma unroll
-    for (int i = 0; i < kRows; ++i)
-      acc[0][S][i] = bad & (0x7ffu << (5 - i)) ? NAN : acc[0][S][i];
+    for (int i = 0; i < kRows; ++i) {
+      const unsigned rows = 0x7ffu << (5 - i);
+      acc[0][S][i] = bad & rows ? NAN : acc[0][S][i];
+      if (kSquares >= 0)
+        acc[max(kSquares, 0)][S][i] =
+            bad & (rows << 16) ? INFINITY : acc[max(kSquares, 0)][S][i];
+    }
   }
   template <int G, int K>
   __device__ __forceinline__ void row(float band, const float (&v)[N]) {
@@ -312,7 +328,8 @@ __device__ __forceinline__ void strip_step(const SsimArgs& a, const float* X,
       const float dm = mx - my, d1 = dm * dm;
       const float A1 = fmaf(2.f, mxy, kC1);
       const float A2 = fmaf(2.f, m[o][3] - mxy, kC2);
-      const float d2 = fmaf(-dm, dm, m[o][2]);
+      // Bounded, so that its reciprocal is not 0 where the squares overflow.
+      const float d2 = fminf(fmaf(-dm, dm, m[o][2]), kBig);
       // Reciprocals are enough here (the term is compared at 1e-5 / 1e-3).
       const float iB1 = __builtin_amdgcn_rcpf(A1 + d1);
       const float iB2 = __builtin_amdgcn_rcpf(A2 + d2);

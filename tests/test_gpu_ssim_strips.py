@@ -111,6 +111,17 @@ def test_gradient_written_over_the_rendering(shape, fused):
     assert float(loss[0]) == pytest.approx(float(loss[1]), rel=1e-9)
 
 
+@pytest.mark.parametrize("shape", [(_views(61, 250), 3, 61, 250), (1, 3, 61, 90)])
+@pytest.mark.parametrize("value", [1e19, -1e20, 1.5e20])
+def test_a_value_whose_square_runs_over(shape, value):
+    """Finite in both forms (strips, tiles): the windows that hold it have an
+    SSIM of 0 and pass no gradient."""
+    x, y = _pair(16, shape)
+    x[0, 1, 37, 80] = value
+    print("case ssim large", shape, value, flush=True)
+    _check(x, y)
+
+
 def test_identical_images_give_exactly_no_gradient():
     x, _ = _pair(17, (_views(61, 250), 3, 61, 250))
     print("case ssim identical", flush=True)
