@@ -43,10 +43,10 @@ class InitMLP:
         self.g = torch.zeros_like(self.w)
         self.step = 0
         # Feature / target normalisation (set by fit_normalisation).
-        self.x_mu = torch.zeros(32, device=device)
-        self.x_sd = torch.ones(32, device=device)
-        self.t_mu = torch.zeros(7, device=device)
-        self.t_sd = torch.ones(7, device=device)
+        self.x_mu = torch.zeros(32, dtype=torch.float32, device=device)
+        self.x_sd = torch.ones(32, dtype=torch.float32, device=device)
+        self.t_mu = torch.zeros(7, dtype=torch.float32, device=device)
+        self.t_sd = torch.ones(7, dtype=torch.float32, device=device)
 
     def fit_normalisation(self, x, t):
         self.x_mu, self.x_sd = x.mean(0), x.std(0).clamp_min(1e-6)
@@ -56,7 +56,8 @@ class InitMLP:
         return ((x - self.x_mu) / self.x_sd).contiguous()
 
     def forward_raw(self, x_norm, cache=None):
-        y = torch.empty(x_norm.shape[0], 7, device=x_norm.device)
+        y = torch.empty(x_norm.shape[0], 7, dtype=torch.float32,
+                        device=x_norm.device)
         R.mlp_fwd(self.w, x_norm, y, cache)
         return y
 
@@ -77,7 +78,8 @@ class InitMLP:
     def predict(self, feats):
         """Initial parameters [M][7] (log-scale 3, opacity logit, RGB 3)."""
         if self._plain(feats):
-            y = torch.empty(feats.shape[0], 7, device=feats.device)
+            y = torch.empty(feats.shape[0], 7, dtype=torch.float32,
+                            device=feats.device)
             R.mlp_predict(self.w, feats, self.x_mu, self.x_sd, self.t_mu,
                           self.t_sd, y)
             return y
@@ -89,7 +91,8 @@ class InitMLP:
         (device tensor)."""
         if self._plain(x, t):
             self.step += 1
-            scratch = torch.empty(x.shape[0] * 142, device=x.device)
+            scratch = torch.empty(x.shape[0] * 142, dtype=torch.float32,
+                                  device=x.device)
             loss = torch.empty(1, dtype=torch.float64, device=x.device)
             R.mlp_train_step(self.w, x, t, self.x_mu, self.x_sd, self.t_mu,
                              self.t_sd, scratch, loss, self.g, self.m, self.v,
@@ -98,7 +101,7 @@ class InitMLP:
         xn = self._xin(x)
         tn = ((t - self.t_mu) / self.t_sd).contiguous()
         M = xn.shape[0]
-        cache = torch.empty(M, 128, device=xn.device)
+        cache = torch.empty(M, 128, dtype=torch.float32, device=xn.device)
         y = self.forward_raw(xn, cache)
         dy = torch.empty_like(y)
         loss = torch.zeros(1, dtype=torch.float64, device=xn.device)

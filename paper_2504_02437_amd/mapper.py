@@ -85,7 +85,7 @@ class Mapper:
         C = pts.shape[0] * 9
         feats = mlp_out = None
         if mlp is not None or features:
-            feats = torch.empty(C, 32, device=self.device)
+            feats = torch.empty(C, 32, dtype=torch.float32, device=self.device)
             R.knn_features(self.params, cam_dev, self.W, self.H, img, pts_d,
                            False, feats)
         if mlp is not None:
