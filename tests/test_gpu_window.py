@@ -228,3 +228,52 @@ def test_window_graph_on_the_benchmark_window_against_the_oracle():
         rast.count_pairs(params)
         torch.cuda.synchronize()
     g.close()
+
+
+@pytest.mark.parametrize("degree,tile,W,H", [
+    (2, 16, 96, 72), (3, 16, 96, 72), (3, 8, 60, 50), (2, 32, 150, 131),
+    (3, 32, 150, 131), (0, 16, 273, 240), (3, 16, 273, 240)])
+def test_window_graph_gradients_in_every_form(degree, tile, W, H):
+    """Degrees 2 and 3, and tiles of 16 past the lines of the blocks (918 in
+    all), 8 and 32, with Gaussians that only some of the three views see: the
+    graph's projection and colour backward read the accumulators that the
+    entry points publish as planar rows.  Gradients of each of three replays
+    as eager (FP32 sums in another order: 1e-5 of a row's largest); a slot
+    left uncleared would show in the replay after."""
+    w = synth.tiny_scene(73, n=900, width=W, height=H, f=0.8 * W,
+                         log_scale_mu=-2.3)
+    w.gaussians = synth.with_sh(w.gaussians, 4, degree, 0.05)
+    c = w.cameras[0]
+    turn = lambda a: np.array([[np.cos(a), 0, np.sin(a)], [0, 1, 0],
+                               [-np.sin(a), 0, np.cos(a)]], np.float32)
+    w.cameras = [synth.Camera((turn(a) @ c.R).astype(np.float32), c.t, c.fx,
+                              c.fy, c.cx, c.cy, W, H) for a in (0.0, 0.5, -0.6)]
+    params = R.ParamBuffer.from_gaussians(w.gaussians, capacity=1000)
+    rast = R.Rasterizer(w.cameras, params.capacity, R.Settings(tile=tile))
+    tgt = torch.from_numpy(np.random.default_rng(7).uniform(
+        size=(3, 3, H, W)).astype(np.float32)).cuda()
+    st = _state(params, rast, tgt)
+    start = _snap(st)
+    _eager(st)
+    torch.cuda.synchronize()
+    ref = _snap(st)
+    seen = (rast.ws.tiles_touched()[:, :900] > 0).sum(0)
+    assert bool((seen == 2).any()) and bool((seen == 3).any())
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        g = _graph(st)
+    for i in range(3):
+        print("case window form", degree, tile, W, H, i, flush=True)
+        _restore(st, start)
+        g.run(stream)
+        torch.cuda.synchronize()
+        got = _snap(st)
+        for k in ("rgb", "T", "nlast"):
+            assert torch.equal(got[k], ref[k]), (i, k)
+        scale = ref["grad"].abs().amax(1, keepdim=True)
+        err = (got["grad"] - ref["grad"]).abs() / (scale + 1e-30)
+        assert float(err.max()) <= 1e-5, (i, float(err.max()))
+        torch.testing.assert_close(got["loss"], ref["loss"], rtol=1e-12, atol=0)
+        st["rast"].count_pairs(st["params"])
+        torch.cuda.synchronize()
+    g.close()
