@@ -155,3 +155,48 @@ def test_sheared_camera_beyond_the_list(corner):
     means = np.repeat(P[[4, corner]], 400, axis=0).T
     means = means + rng.normal(0, 1e-3, size=means.shape)
     _check(means.astype(np.float32), cam, pts, False)
+
+
+@pytest.mark.parametrize("out", [50.0, 1000.0, 3e4])
+@pytest.mark.parametrize("centre_only", [False, True])
+def test_far_from_the_origin(out, centre_only):
+    """Camera and map away from the world's origin: the same neighbours as
+    the oracle's, and (in the second test) without every mean in reach."""
+    rng = np.random.default_rng(11)
+    print("case near far out", out, centre_only, flush=True)
+    c = _camera(600, 400, 300.0)
+    shift = np.array([out, -0.7 * out, 0.4 * out])
+    t = (c.t - np.asarray(c.R, np.float64) @ shift).astype(np.float32)
+    cam = synth.Camera(c.R, t, c.fx, c.fy, c.cx, c.cy, c.width, c.height)
+    means = synth.room_gaussians(rng, 20000).mean + shift[:, None]
+    _check(means.astype(np.float32), cam, _pts(rng, cam, 40), centre_only)
+
+
+def test_bounds_are_as_tight_far_from_the_origin():
+    """1 km out the neighbour search takes no more than three times as long as
+    at the origin (every mean in reach: a hundred times)."""
+    us = []
+    for out in (0.0, 1000.0):
+        rng = np.random.default_rng(12)
+        print("case near far out time", out, flush=True)
+        c = _camera(600, 400, 300.0)
+        shift = np.full(3, out)
+        t = (c.t - np.asarray(c.R, np.float64) @ shift).astype(np.float32)
+        cam_d = R.cameras_to_device([synth.Camera(c.R, t, c.fx, c.fy, c.cx,
+                                                  c.cy, c.width, c.height)])
+        mean = synth.room_gaussians(rng, 200000).mean + shift[:, None]
+        params = R.ParamBuffer(200000, n=200000)
+        params.data[0:3] = _dev(mean.astype(np.float32))
+        pts = _dev(_pts(rng, c, 96))
+        img = torch.zeros(3, c.height, c.width, device="cuda")
+        feats = torch.empty(96 * 9, 32, device="cuda")
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        for k in range(4):
+            if k == 1:
+                a.record()
+            R.knn_features(params, cam_d, c.width, c.height, img, pts, False, feats)
+        b.record()
+        torch.cuda.synchronize()
+        us.append(a.elapsed_time(b) / 3 * 1e3)
+    print("us at 0 and 1000 m", us)
+    assert us[1] <= 3 * us[0]
