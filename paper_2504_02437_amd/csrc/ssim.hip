@@ -494,9 +494,10 @@ void k_ssim(SsimArgs a) {
 }
 
 // How the planes are split: threads of a workgroup (20 columns more than it
-// writes) and the rows that it writes.
+// writes), the rows that it writes, and about how long the pass takes.
 struct Split {
   int nt, strips, rows;
+  double us;
 };
 
 // The split of the least cost, in steps of a workgroup.  A workgroup takes
@@ -520,9 +521,10 @@ Split split_planes(int planes, int H, int W) {
       const int g = (int)((groups + parts - 1) / parts);
       const long long n = columns * ((groups + g - 1) / g);
       const long long waves = (n + filled - 1) / filled;
-      const double cost = (waves / 2 * 1.3 + waves % 2) * (g + kLag - 1) + 0.002 * n;
+      const double rounds = waves / 2 * 1.3 + waves % 2;
+      const double cost = rounds * (g + kLag - 1) + 0.002 * n;
       if (!best.nt || cost < least) {
-        best = {nt, strips, kRows * g};
+        best = {nt, strips, kRows * g, 8.1 + 2.6 * rounds * (g + 1) + 0.0076 * n};
         least = cost;
       }
     }
@@ -552,9 +554,18 @@ hipError_t launch_loss_ssim(const float* rgb, const float* target, int V,
 // 64 x 35 (90 tiles) 12.5 / 15.9, five 128 x 70 (150) 13.7 / 15.8, one 256 x
 // 204 (156) 13.9 / 15.9, three 256 x 204 (468) 21.3 / 22.8; ten 100 x 80 (300)
 // 18.1 / 20.6; one 377 x 251 (288) 21.2 / 17.0, eight 256 x 204 (1,248) 38 / 33.
-bool use_tiles(int V, int H, int W) {
-  const long long tiles = 3LL * V * ((W + 63) / 64) * ((H + 15) / 16);
-  return tiles <= 256 || (W <= 256 && tiles <= 600);
+// Past 600 tiles widths that fill their strips badly (45-64, 109-128 or
+// 237-256 columns) are still faster in tiles; up to where depends on what the
+// planes split into, so the two times are estimated (within 15 % of 350 sizes
+// up to 3,000 tiles with one tile per workgroup).  Seven 256 x 140 (756 tiles)
+// 26.4 / 29.7, five 237 x 189 (720) 26.2 / 29.8, 51 64 x 64 (612) 22.7 / 32.1,
+// 433 64 x 16 (1,299) 37.9 / 46.4; ten 236 x 129 (1,080) 34.9 / 23.3.
+static bool use_tiles(int V, int H, int W) {
+  const long long plane = (long long)((W + 63) / 64) * ((H + 15) / 16);
+  const long long tiles = 3 * V * plane;
+  if (tiles <= 600) return tiles <= 256 || W <= 256;
+  return plane <= 64 && tiles <= 3000 &&
+         10.7 + 0.0208 * tiles < split_planes(3 * V, H, W).us;
 }
 
 hipError_t launch_loss_colour(const float* rgb, const float* target, int V,

@@ -111,7 +111,65 @@ def test_gradient_written_over_the_rendering(shape, fused):
     assert float(loss[0]) == pytest.approx(float(loss[1]), rel=1e-9)
 
 
-@pytest.mark.parametrize("shape", [(_views(61, 250), 3, 61, 250), (1, 3, 61, 90)])
+# Always taken in strips: past 256 tiles, more than 64 of them in a plane; or
+# more than 3,000 in all.
+STRIPS = (1, 3, 250, 344)
+MANY = [(3000 // (3 * ((W + 63) // 64) * ((H + 15) // 16)) + 1, 3, H, W)
+        for H, W in ((11, 44), (12, 45), (13, 88), (16, 109), (33, 217),
+                     (50, 237), (330, 44))]
+
+
+@pytest.mark.parametrize("shape", MANY)
+def test_strip_edges_of_many_views(shape):
+    """Views enough for strips whatever the width fills: the first, one in the
+    middle and the last against the oracle."""
+    x, y = _pair(19, shape)
+    print("case ssim many", shape, flush=True)
+    loss, ssim, g = _gpu(x, y, 0.2)
+    ref_ssim = OS.ssim_map(x, y).reshape(shape[0], -1).mean(1)
+    assert np.abs(ssim - ref_ssim).max() <= 1e-5
+    assert loss == pytest.approx(0.2 * np.sum(1.0 - ref_ssim), rel=1e-5)
+    for k in (0, shape[0] // 2, shape[0] - 1):
+        ref = OS.loss_ssim(x[k:k + 1].astype(np.float64), y[k:k + 1], 0.2)[1]
+        tol = 1e-3 * np.maximum(np.abs(ref), 1e-2 * np.abs(ref).max()) + 1e-30
+        assert np.all(np.abs(g[k:k + 1] - ref) <= tol)
+
+
+@pytest.mark.parametrize("which", range(3))
+def test_misaligned_strips(which):
+    """test_misaligned_images at a size that is always taken in strips."""
+    x, y = _pair(20, STRIPS)
+    n = x.size
+    buf = [torch.zeros(n + 4, device="cuda") for _ in range(3)]
+    loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+    ref = _colour(x, y, 0.8, 0.2, True)
+    t = [b[int(i == which):][:n].view(STRIPS) for i, b in enumerate(buf)]
+    t[0].copy_(torch.from_numpy(x))
+    t[1].copy_(torch.from_numpy(y))
+    print("case colour misaligned strips", which, flush=True)
+    R.loss_colour(t[0], t[1], 0.8, 0.2, t[2], loss)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(t[2].cpu().numpy(), ref[3])
+    assert all(float(b[-1]) == 0.0 for b in buf)
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("at", [(37, 120), (0, 0), (249, 1), (120, 343)])
+def test_a_value_that_is_not_finite_stays_in_its_windows_of_strips(at, value):
+    x, y = _pair(21, STRIPS)
+    good = _colour(x, y, 0.8, 0.2, True)[3][0, 1]
+    x[0, 1, at[0], at[1]] = value
+    print("case strips not finite", at, value, flush=True)
+    loss, _, _, g = _colour(x, y, 0.8, 0.2, True)
+    r, c = np.mgrid[0:STRIPS[2], 0:STRIPS[3]]
+    near = np.maximum(abs(r - at[0]), abs(c - at[1])) <= 10
+    assert np.isnan(loss)
+    assert np.isnan(g[0, 1][near]).all()
+    np.testing.assert_array_equal(g[0, 1][~near], good[~near])
+    assert np.isfinite(g[0, 0]).all() and np.isfinite(g[0, 2]).all()
+
+
+@pytest.mark.parametrize("shape", [STRIPS, (1, 3, 61, 90)])
 @pytest.mark.parametrize("value", [1e19, -1e20, 1.5e20])
 def test_a_value_whose_square_runs_over(shape, value):
     """Finite in both forms (strips, tiles): the windows that hold it have an
@@ -123,7 +181,7 @@ def test_a_value_whose_square_runs_over(shape, value):
 
 
 def test_identical_images_give_exactly_no_gradient():
-    x, _ = _pair(17, (_views(61, 250), 3, 61, 250))
+    x, _ = _pair(17, STRIPS)
     print("case ssim identical", flush=True)
     loss, ssim, g = _gpu(x, x, 0.2)
     assert abs(loss) < 1e-6 * x.shape[0] and np.all(np.abs(ssim - 1.0) < 1e-6)
@@ -136,7 +194,7 @@ def test_no_further_from_64_bits_than_in_tiles(noise):
     gradient's root mean square error is no larger (7e5 values of a view's
     rounding errors, which two draws give to well within 1 %)."""
     rng = np.random.default_rng(18)
-    V, H, W = 6, 160, 256
+    V, H, W = 6, 160, 300
     r, c = np.mgrid[0:H, 0:W]
     y = 0.5 + 0.45 * np.sin(r / 9.0 + rng.uniform(0, 6, (V, 3, 1, 1))) * np.cos(c / 13.0)
     x = np.clip(y + noise * rng.normal(size=y.shape), 0, 1).astype(np.float32)
