@@ -193,7 +193,10 @@ typedef struct gs_workspace_view {
   float* grad_colour;
 } gs_workspace_view;
 
-/* Host only.  Bytes of device memory a workspace for `geo` needs. */
+/* Host only.  Bytes of device memory a workspace for `geo` needs: 160 per
+ * view and Gaussian of the capacity (records and boxes 64, screen-space
+ * gradients 32, the backward's FP64 accumulators 64), 92 per Gaussian, 20 per
+ * key of the capacity, and the tiles' and chunks' counts. */
 GS_API int gs_workspace_size(const gs_geometry* geo, size_t* bytes);
 
 /* Host only.  Creates a handle over `device_buffer` (at least

@@ -17,7 +17,7 @@
 // far from the world's origin (their differences' rounding, 2^-24 of each,
 // moves a squared distance by 2^-22 of the squares at most; 300k means 1 km
 // out, all of them in reach of every patch from the origin: 249 us for the
-// distance test and 6.1 ms for the neighbours' pass, now 29 and 50).
+// distance test and 6.1 ms for the neighbours' pass, now 28 and 51).
 //
 // Every pair in FP64 on the vector units took 113 us (distance test) and 320
 // us (neighbours) for 96 patches against 300k means; now 16 us, and 35 us in
@@ -36,7 +36,10 @@ typedef float f4v __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 16, kThreads = 64 * kWaves;
 constexpr int kPatches = 16;   // patches per workgroup (matrix columns)
-constexpr int kAhead = 5;      // groups of 64 means in flight per wave
+// Groups of 64 means in flight per wave: 5 take a slice of 300k means in one
+// go; with 3, 4, 6 or 8 the searches of 50k to 1M means are within 3 % (20,
+// at 70 registers more, leaves half the waves: 37 us against 16).
+constexpr int kAhead = 5;
 constexpr float kUp = 1.f + 0x1p-19f, kDown = 1.f - 0x1p-19f;
 constexpr float kTiny = 1e-30f;   // covers squares that underflow
 constexpr float kHuge = 1e37f;    // squares below it cannot overflow the sum
