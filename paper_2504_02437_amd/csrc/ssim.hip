@@ -34,11 +34,13 @@
 // Bound by the horizontal sums: 308 FMAs per four pixels in a row plus the
 // pointwise terms, about 500 vector instructions, at two waves per SIMD (240
 // registers for the two sets of 28 open sums; at three the sums spill, 2
-// times slower).  Two sets of LDS buffers instead of three, with a barrier
+// times slower), which issue 0.47 of what the vector units take, with the
+// matrix units busy 0.15 of the time: the chain of a step between its three
+// barriers is not covered by one other wave.  Two sets of LDS buffers instead of three, with a barrier
 // more per step, was 3 % slower.  In place of a statistics and a gradient
 // kernel with the derivative maps in memory between them: ten 680 x 1200 views
-// 282 us (was 405; 9.8 MB per plane in and out), one 44 (92), ten 480 x 640
-// 107 (161), one 251 x 377 17.3 (21.2).  Small inputs keep those two kernels
+// 284 us (was 405; 9.8 MB per plane in and out), one 41 (92), ten 480 x 640
+// 103 (161), one 251 x 377 16.8 (21.2).  Small inputs keep those two kernels
 // (ssim_tiles.hip, use_tiles).
 
 #include <float.h>
