@@ -145,7 +145,7 @@ __device__ __forceinline__ void load_batch(const NearArgs& a, int begin,
   for (int u = 0; u < kAhead; ++u) {
     const int g = min(begin + 64 * (g0 + u * kWaves) + ((int)threadIdx.x & 63), end - 1);
     b.x[u] = a.mean[g];
-    b.y[u] = a.mean[a.cap + g];
+    b.y[u] = a.mean[(size_t)a.cap + g];
     b.z[u] = a.mean[2 * (size_t)a.cap + g];
   }
 }
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(kThreads) void k_nearest(NearArgs a) {
   __shared__ float mid[kPatches][3];
   __shared__ float part[kWaves][kPatches];
   __shared__ float reach[kPatches];
-  __shared__ uint32_t within[kWithin];   // patch << 27 | mean - begin
+  __shared__ uint32_t within[kWithin];   // patch << 28 | mean - begin (2^28: eight slices)
   __shared__ int n_within;
   const int tid = threadIdx.x, lane = tid & 63;
   const int p0 = blockIdx.y * kPatches;
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(kThreads) void k_nearest(NearArgs a) {
   const float r = reach[p];
   auto exact = [&](int pp, int i, int g) {
     if (best[pp][i] == ~0ull) return;   // not tested
-    const double d2 = dist2(X[pp][i], a.mean[g], a.mean[a.cap + g],
+    const double d2 = dist2(X[pp][i], a.mean[g], a.mean[(size_t)a.cap + g],
                             a.mean[2 * (size_t)a.cap + g]);
     if (d2 == d2)
       atomicMin(&best[pp][i], (unsigned long long)__double_as_longlong(d2));
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(kThreads) void k_nearest(NearArgs a) {
       if (d[q] > r || g >= end) continue;
       const int at = atomicAdd(&n_within, 1);
       if (at < kWithin) {
-        within[at] = ((uint32_t)p << 27) | (uint32_t)(g - begin);
+        within[at] = ((uint32_t)p << 28) | (uint32_t)(g - begin);
       } else {
         for (int i = 0; i < a.per; ++i) exact(p, i, g);
       }
@@ -336,7 +336,7 @@ __global__ __launch_bounds__(kThreads) void k_nearest(NearArgs a) {
   for (int j = tid; j < jobs; j += kThreads) {
     const int e = j / a.per;
     const uint32_t w = within[e];
-    exact((int)(w >> 27), j - e * a.per, begin + (int)(w & 0x7ffffffu));
+    exact((int)(w >> 28), j - e * a.per, begin + (int)(w & 0xfffffffu));
   }
   __syncthreads();
   if (live) atomicMin(&a.d2bits[(p0 + cp) * a.per + ci], best[cp][ci]);
@@ -589,7 +589,7 @@ __global__ __launch_bounds__(576) void k_knn_select(NearArgs a) {
   double X[3];
   back_project(*a.cam, c, X);
   auto exact = [&](int g) {
-    return dist2(X, a.mean[g], a.mean[a.cap + g], a.mean[2 * (size_t)a.cap + g]);
+    return dist2(X, a.mean[g], a.mean[(size_t)a.cap + g], a.mean[2 * (size_t)a.cap + g]);
   };
   // Neighbour j of the candidate, found by some lane: its terms of the
   // features go to slot j.
